@@ -35,12 +35,12 @@ namespace {
 
 constexpr uint64_t kDefaultStaging = 512ull << 20;
 constexpr uint32_t kGridHost = 128;     // enough outstanding 16-B accesses to fill the host link
-// Workgroups of an HBM-to-HBM gather (d = 0) or scatter (d = 1).  Measured in
-// the full-size pipelined rebalance: on runs of 32 KiB and more the gather is
-// fastest with one run per workgroup (a 1 GiB staging half of 32 KiB runs:
-// 32 768 workgroups, 4-5% faster than 16 384 and 6% faster than 8 192) while
-// the scatter loses 1-2% there against 16 384; on 16 KiB runs 16 384
-// workgroups (about four runs each) beat 32 768 by 2% and 8 192 by 3%.
+// Most workgroups of an HBM-to-HBM gather (d = 0) or scatter (d = 1) of one
+// staging half.  Measured in the full-size pipelined rebalance: on runs of
+// 32 KiB and more the gather is fastest with one run per workgroup (a 1 GiB
+// staging half of 32 KiB runs: 32 768 workgroups, 4-5% faster than 16 384 and
+// 6% faster than 8 192) while the scatter loses 1-2% there against 16 384; on
+// shorter runs 16 384 workgroups beat 32 768 by 2% and 8 192 by 3%.
 uint32_t grid_device(uint64_t run, int d) { return run >= (32u << 10) && d == 0 ? 32768u : 16384u; }
 constexpr uint64_t kTimeOnly = ~0ull;
 
@@ -86,13 +86,17 @@ struct mori_ctx {
   uint32_t* pstate = nullptr;
   uint32_t* out_src = nullptr;
   uint32_t* in_dst = nullptr;
+  uint32_t* ord = nullptr;
+  uint32_t* out_ord = nullptr;
+  uint32_t* in_ord = nullptr;
   uint64_t* tile_cnt = nullptr;
   uint64_t* tile_base = nullptr;
-  uint64_t* addr_stage[2] = {nullptr, nullptr};
   uint64_t* addr_dev[2] = {nullptr, nullptr};
   uint32_t* swap_err = nullptr;  // [2] per direction
   DevRange* ranges_dev = nullptr;
-  uint64_t* addr_pinned = nullptr;  // [2][max_programs]
+  SwapRange* swap_range = nullptr;      // [2] per direction
+  uint64_t* addr_pinned = nullptr;      // [2][max_programs]
+  uint64_t* addr_pinned_dev = nullptr;  // the same as the device addresses it
   uint8_t* staging[2] = {nullptr, nullptr};  // per direction, two halves
   uint64_t staging_bytes = 0;
   hipStream_t cstream[2] = {nullptr, nullptr};  // per direction: the copy-engine copies
@@ -105,6 +109,7 @@ struct mori_ctx {
   bool out_recorded = false, in_recorded = false, addr_pending[2] = {false, false};
   uint32_t P = 0;
   const uint32_t* tbl_off = nullptr;
+  uint32_t tbl_len = 0;
   int last_hip_error = 0;
   uint32_t last_mode = 0;
   // kernel timing (opt-in)
@@ -236,25 +241,30 @@ extern "C" int mori_create(const mori_pool* pool, uint32_t max_programs, uint64_
     return r;
   };
   const size_t o_base = take(4 * pm), o_pstate = take(4 * NB), o_out_src = take(4 * NB), o_in_dst = take(4 * NB);
+  const size_t o_ord = take(4 * pm), o_out_ord = take(4 * NB), o_in_ord = take(4 * NB);
   const size_t o_tc = take(16ull * c->ntiles), o_tb = take(16ull * c->ntiles);
-  const size_t o_as0 = take(8 * pm), o_as1 = take(8 * pm), o_ad0 = take(8 * pm), o_ad1 = take(8 * pm);
-  const size_t o_err = take(8), o_rng = take(sizeof(DevRange) * MORI_MAX_RANGES);
+  const size_t o_ad0 = take(8 * pm), o_ad1 = take(8 * pm);
+  const size_t o_err = take(8), o_rng = take(sizeof(DevRange) * MORI_MAX_RANGES), o_sr = take(2 * sizeof(SwapRange));
   if ((e = hipMalloc(&c->scratch, o)) != hipSuccess) return fail(e);
   c->base = reinterpret_cast<uint32_t*>(c->scratch + o_base);
   c->pstate = reinterpret_cast<uint32_t*>(c->scratch + o_pstate);
   c->out_src = reinterpret_cast<uint32_t*>(c->scratch + o_out_src);
   c->in_dst = reinterpret_cast<uint32_t*>(c->scratch + o_in_dst);
+  c->ord = reinterpret_cast<uint32_t*>(c->scratch + o_ord);
+  c->out_ord = reinterpret_cast<uint32_t*>(c->scratch + o_out_ord);
+  c->in_ord = reinterpret_cast<uint32_t*>(c->scratch + o_in_ord);
   c->tile_cnt = reinterpret_cast<uint64_t*>(c->scratch + o_tc);
   c->tile_base = reinterpret_cast<uint64_t*>(c->scratch + o_tb);
-  c->addr_stage[0] = reinterpret_cast<uint64_t*>(c->scratch + o_as0);
-  c->addr_stage[1] = reinterpret_cast<uint64_t*>(c->scratch + o_as1);
   c->addr_dev[0] = reinterpret_cast<uint64_t*>(c->scratch + o_ad0);
   c->addr_dev[1] = reinterpret_cast<uint64_t*>(c->scratch + o_ad1);
   c->swap_err = reinterpret_cast<uint32_t*>(c->scratch + o_err);
   c->ranges_dev = reinterpret_cast<DevRange*>(c->scratch + o_rng);
+  c->swap_range = reinterpret_cast<SwapRange*>(c->scratch + o_sr);
   if ((e = hipMemset(c->scratch, 0, o)) != hipSuccess) return fail(e);
   if ((e = hipMemset(c->blob_dev, 0, c->L.total)) != hipSuccess) return fail(e);
-  if ((e = hipHostMalloc(&c->addr_pinned, 16 * pm, hipHostMallocDefault)) != hipSuccess) return fail(e);
+  if ((e = hipHostMalloc(&c->addr_pinned, 16 * pm, hipHostMallocMapped)) != hipSuccess) return fail(e);
+  if ((e = hipHostGetDevicePointer(reinterpret_cast<void**>(&c->addr_pinned_dev), c->addr_pinned, 0)) != hipSuccess)
+    return fail(e);
   for (int d = 0; d < 2; ++d)
     if ((e = hipMalloc(&c->staging[d], staging_bytes)) != hipSuccess) return fail(e);
   for (hipEvent_t* ev : {&c->ev_plan, &c->ev_out, &c->ev_in, &c->ev_addr[0], &c->ev_addr[1], &c->ev_start[0],
@@ -384,6 +394,9 @@ extern "C" int mori_rank_partition(mori_ctx* ctx, const mori_programs* pr, const
   a.pstate = ctx->pstate;
   a.out_src = ctx->out_src;
   a.in_dst = ctx->in_dst;
+  a.ord = ctx->ord;
+  a.out_ord = ctx->out_ord;
+  a.in_ord = ctx->in_ord;
   a.tile_cnt = ctx->tile_cnt;
   a.tile_base = ctx->tile_base;
   a.swap_err = ctx->swap_err;
@@ -395,6 +408,7 @@ extern "C" int mori_rank_partition(mori_ctx* ctx, const mori_programs* pr, const
   ctx->out_enqueued = ctx->in_enqueued = false;
   ctx->P = P;
   ctx->tbl_off = pr->tbl_off;
+  ctx->tbl_len = pr->tbl_len;
   return MORI_OK;
 }
 
@@ -476,16 +490,6 @@ bool host_check(const mori_ctx* c, const uint64_t* addr, const uint32_t* progs, 
   return true;
 }
 
-int stage_addresses(mori_ctx* c, int d, const uint64_t* addr, hipStream_t s) {
-  if (c->addr_pending[d]) HIP_TRY(c, hipEventSynchronize(c->ev_addr[d]));
-  uint64_t* pin = c->addr_pinned + (size_t)d * c->max_programs;
-  std::memcpy(pin, addr, sizeof(uint64_t) * c->P);
-  if (c->P) HIP_TRY(c, hipMemcpyAsync(c->addr_stage[d], pin, sizeof(uint64_t) * c->P, hipMemcpyHostToDevice, s));
-  HIP_TRY(c, hipEventRecord(c->ev_addr[d], s));
-  c->addr_pending[d] = true;
-  return MORI_OK;
-}
-
 // Copies of one staging half, issued in unit order; a segment that continues
 // the previous one on both sides (host buffers of consecutive programs that
 // are adjacent, as a first-fit arena hands them out) joins it, so a half
@@ -525,10 +529,11 @@ SwapArgs swap_args(const mori_ctx* c, int d) {
   a.NB = c->pool.num_blocks;
   a.run = c->run;
   a.LC = c->LC;
-  a.sum = c->sum_dev();
+  a.range = c->swap_range + d;
   a.prog = c->dev<uint32_t>(d ? c->L.in_prog : c->L.out_prog);
   a.pg_base = c->dev<uint32_t>(d ? c->L.in_base : c->L.out_base);
   a.pages = d ? c->in_dst : c->out_src;
+  a.ord = d ? c->in_ord : c->out_ord;
   a.addr = c->addr_dev[d];
   a.swap_err = c->swap_err;
   return a;
@@ -556,20 +561,47 @@ int timed_swap_launch(mori_ctx* c, int d, const SwapArgs& a, uint32_t grid, hipS
   return MORI_OK;
 }
 
-int translate(mori_ctx* c, int d, hipStream_t s) {
+// Resolves the direction's addresses on the device.  The kernel reads the
+// caller's table where the host puts it, in pinned memory (a copy to the
+// device first cost a copy kernel and its two launch gaps per direction), so
+// the table may be overwritten once the kernel has finished.
+int translate(mori_ctx* c, int d, const uint64_t* addr, hipStream_t s) {
+  if (c->addr_pending[d]) HIP_TRY(c, hipEventSynchronize(c->ev_addr[d]));
+  std::memcpy(c->addr_pinned + (size_t)d * c->max_programs, addr, sizeof(uint64_t) * c->P);
   TranslateArgs t{};
   t.sum = c->sum_dev();
+  t.pg_base = c->dev<uint32_t>(d ? c->L.in_base : c->L.out_base);
+  t.ord = d ? c->in_ord : c->out_ord;
+  t.range = c->swap_range + d;
+  t.LC = c->LC;
   t.prog = c->dev<uint32_t>(d ? c->L.in_prog : c->L.out_prog);
   t.dir_in = d;
   t.tbl_off = c->tbl_off;
   t.block_bytes = c->block_bytes;
-  t.addr_in = c->addr_stage[d];
+  t.addr_in = c->addr_pinned_dev + (size_t)d * c->max_programs;
   t.addr_out = c->addr_dev[d];
   t.ranges = c->ranges_dev;
   t.nranges = (uint32_t)c->ranges.size();
   t.swap_err = c->swap_err;
   HIP_TRY(c, launch_translate(t, s));
+  HIP_TRY(c, hipEventRecord(c->ev_addr[d], s));
+  c->addr_pending[d] = true;
   return MORI_OK;
+}
+
+// Workgroups of a kernel-direct launch, whose size the host does not know.
+// Between HBM buffers: enough for one pass over every page that could move,
+// since a workgroup without a run still costs its launch (250 MiB of 32 KiB
+// runs: 242 us a pair of rebalances with the bound, 448 without), at most
+// 32 768 on runs of 32 KiB and more and 16 384 on shorter ones (6 GiB of
+// 72 KiB runs: 4.18 ms with 32 768 both ways, 4.24 with the scatter at 16 384,
+// 4.20 with 65 536; 1.5 GiB of 4 KiB runs: 1.26 ms with 16 384, 1.34 with
+// 32 768, 1.28 with 8 192).
+uint32_t grid_direct(const mori_ctx* c, bool device_only) {
+  if (!device_only) return kGridHost;
+  const uint64_t units = std::min<uint64_t>(c->tbl_len, c->pool.num_blocks) * c->LC;
+  const uint64_t need = units / swap_runs_per_workgroup(c->run, false) + 1;
+  return (uint32_t)std::min<uint64_t>(need, c->run >= (32u << 10) ? 32768u : 16384u);
 }
 
 }  // namespace
@@ -584,12 +616,11 @@ extern "C" int mori_kv_swap_out(mori_ctx* ctx, const uint64_t* host_dst, uint32_
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   if (m == MORI_COPY_KERNEL) {
     HIP_TRY(ctx, hipStreamWaitEvent(s, ctx->ev_plan, 0));
-    int rc = stage_addresses(ctx, 0, host_dst, s);
+    int rc = translate(ctx, 0, host_dst, s);
     if (rc) return rc;
-    if ((rc = translate(ctx, 0, s))) return rc;
     SwapArgs a = swap_args(ctx, 0);
     a.host_link = !device_only;
-    if ((rc = timed_swap_launch(ctx, 0, a, device_only ? grid_device(ctx->run, 0) : kGridHost, s, 0))) return rc;
+    if ((rc = timed_swap_launch(ctx, 0, a, grid_direct(ctx, device_only), s, 0))) return rc;
   } else {
     HIP_TRY(ctx, hipEventSynchronize(ctx->ev_plan));
     const DevSummary* sh = ctx->sum_host();
@@ -655,12 +686,11 @@ extern "C" int mori_kv_swap_in(mori_ctx* ctx, const uint64_t* host_src, uint32_t
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   if (m == MORI_COPY_KERNEL) {
     HIP_TRY(ctx, hipStreamWaitEvent(s, ctx->ev_plan, 0));
-    int rc = stage_addresses(ctx, 1, host_src, s);
+    int rc = translate(ctx, 1, host_src, s);
     if (rc) return rc;
-    if ((rc = translate(ctx, 1, s))) return rc;
     SwapArgs a = swap_args(ctx, 1);
     a.host_link = !device_only;
-    const uint32_t grid = device_only ? grid_device(ctx->run, 1) : kGridHost;
+    const uint32_t grid = grid_direct(ctx, device_only);
     a.part = 1;  // slots on pages that were free before the step
     if ((rc = timed_swap_launch(ctx, 1, a, grid, s, 0))) return rc;
     HIP_TRY(ctx, hipStreamWaitEvent(s, ctx->ev_out, 0));

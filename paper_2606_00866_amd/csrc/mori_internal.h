@@ -67,6 +67,9 @@ struct PlanArgs {
   uint32_t* pstate;       // [NB]
   uint32_t* out_src;      // [pages_out] old page of each out page index
   uint32_t* in_dst;       // [need] page of each slot
+  uint32_t* ord;          // per program: its index in the swap-out or swap-in list (OUT, IN)
+  uint32_t* out_ord;      // [pages_out] swap-out list index of each out page index
+  uint32_t* in_ord;       // [pages_in] swap-in list index of each slot
   uint64_t* tile_cnt;     // [2 ntiles]: packed (free-before, dropped << 32), then free-later counts
   uint64_t* tile_base;    // [2 ntiles] exclusive prefixes of both halves of tile_cnt
   uint32_t* swap_err;     // [2] swap-out, swap-in address errors; cleared by every plan
@@ -81,15 +84,24 @@ __device__ inline T* host_mirror(const PlanArgs& a, T* blob_ptr) {
   return reinterpret_cast<T*>(reinterpret_cast<char*>(blob_ptr) + a.host_delta);
 }
 
+// Unit ranges of a kernel-direct swap, written by its translation (all zero
+// after a failed plan): [0, total) is the whole direction, [0, first_end) the
+// first part of a swap-in and [second_begin, total) the second.
+struct SwapRange {
+  uint64_t total, first_end, second_begin;
+  uint64_t nf;  // slots below it need no wait
+};
+
 // Everything a swap kernel reads.
 struct SwapArgs {
   uint8_t* pool;
   uint64_t NB, run;
   uint32_t LC;              // layers * planes
-  const DevSummary* sum;
+  const SwapRange* range;   // kernel-direct mode: this direction's unit ranges
   const uint32_t* prog;     // out_prog or in_prog
   const uint32_t* pg_base;  // out_pg_base or in_pg_base
   const uint32_t* pages;    // out_src (by out-page index) or in_dst (by slot)
+  const uint32_t* ord;      // out_ord or in_ord: list index of each out-page index / slot
   const uint64_t* addr;     // device address of each program's host buffer
   const uint32_t* swap_err; // [2] address errors found by the swap-out's and the swap-in's translation
   uint8_t* staging;         // non-null: chunk staging buffer (copy-engine mode)
@@ -100,11 +112,15 @@ struct SwapArgs {
 
 struct TranslateArgs {
   const DevSummary* sum;
+  const uint32_t* pg_base;  // out_pg_base or in_pg_base
+  const uint32_t* ord;      // out_ord or in_ord
+  SwapRange* range;         // this direction's
+  uint32_t LC;
   const uint32_t* prog;     // out_prog or in_prog (count n_out / n_in)
   int dir_in;               // 0 out, 1 in
   const uint32_t* tbl_off;
   uint64_t block_bytes;
-  const uint64_t* addr_in;  // [P] caller addresses (copied to the device)
+  const uint64_t* addr_in;  // [P] caller addresses, in pinned host memory
   uint64_t* addr_out;       // [P] translated device addresses
   const DevRange* ranges;
   uint32_t nranges;
@@ -139,6 +155,7 @@ hipError_t launch_pages(const PlanArgs& a, hipStream_t s);
 hipError_t launch_translate(const TranslateArgs& a, hipStream_t s);
 hipError_t launch_swap_out(const SwapArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_swap_in(const SwapArgs& a, uint32_t grid, hipStream_t s);
+uint32_t swap_runs_per_workgroup(uint64_t run, bool host_link);  // per pass of a swap kernel
 hipError_t launch_evict(uint32_t N, const uint8_t* type, const uint64_t* last_access, const uint32_t* size,
                         uint64_t unit_bytes, uint32_t tier, uint64_t need, void* workspace, uint32_t* order,
                         uint64_t* prefix, uint32_t* result, hipStream_t s);

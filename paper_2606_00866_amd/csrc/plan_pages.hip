@@ -79,8 +79,12 @@ __global__ __launch_bounds__(WG) void pages_claim_kernel(PlanArgs a) {
     if (old & (PS_FREE | PS_OWNED)) err |= MORI_DEV_PAGE_DUP;
     if (c == MORI_CAT_OUT) {
       const uint32_t k = a.base[p] + (e - a.tbl_off[p]);
-      if (k < a.NB) a.out_src[k] = pg;  // more owned blocks than pages implies a duplicate
-      else err |= MORI_DEV_PAGE_DUP;
+      if (k < a.NB) {  // more owned blocks than pages implies a duplicate
+        a.out_src[k] = pg;
+        a.out_ord[k] = a.ord[p];
+      } else {
+        err |= MORI_DEV_PAGE_DUP;
+      }
     }
   }
   if (err) atomicOr(&a.sum->error, err);
@@ -265,7 +269,11 @@ __global__ __launch_bounds__(WG) void commit_kernel(PlanArgs a) {
     const uint32_t p = find_program(a.tbl_off, a.P, e);
     const uint8_t c = a.cat[p];
     if (c == MORI_CAT_OUT || c == MORI_CAT_DROP_GPU) a.tbl[e] = MORI_NO_PAGE;
-    else if (c == MORI_CAT_IN || c == MORI_CAT_ADMIT_GPU) a.tbl[e] = a.in_dst[a.base[p] + (e - a.tbl_off[p])];
+    else if (c == MORI_CAT_IN || c == MORI_CAT_ADMIT_GPU) {
+      const uint32_t slot = a.base[p] + (e - a.tbl_off[p]);
+      a.tbl[e] = a.in_dst[slot];
+      if (c == MORI_CAT_IN) a.in_ord[slot] = a.ord[p];
+    }
   }
   for (uint32_t p = blockIdx.x * WG + threadIdx.x; p < a.P; p += gridDim.x * WG) a.tier[p] = a.tier_new[p];
 }
@@ -273,9 +281,24 @@ __global__ __launch_bounds__(WG) void commit_kernel(PlanArgs a) {
 // Resolves every moving program's caller address through the registered
 // ranges; a buffer that is not 16-B aligned or not wholly inside one range
 // sets MORI_DEV_HOST_ADDR and the swap kernels then do nothing.
+// It also leaves the direction's unit ranges for the swap kernels.
 __global__ __launch_bounds__(WG) void translate_kernel(TranslateArgs t) {
-  if (t.sum->error) return;
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (t.sum->error) {
+    if (first) *t.range = SwapRange{};
+    return;
+  }
   const uint32_t n = t.dir_in ? t.sum->n_in : t.sum->n_out;
+  if (first) {
+    const uint64_t slots = n ? t.pg_base[n] : 0, LC = t.LC;
+    const uint64_t nf = t.sum->pages_free_before + t.sum->pages_dropped;
+    SwapRange r{slots * LC, slots * LC, slots * LC, nf};
+    if (nf < slots) {  // the program that holds slot nf - 1 ends the first part, the one with slot nf begins the second
+      r.first_end = nf ? (uint64_t)t.pg_base[t.ord[nf - 1] + 1] * LC : 0;
+      r.second_begin = (uint64_t)t.pg_base[t.ord[nf]] * LC;
+    }
+    *t.range = r;
+  }
   uint32_t err = 0;
   for (uint32_t j = blockIdx.x * WG + threadIdx.x; j < n; j += gridDim.x * WG) {
     const uint32_t p = t.prog[j];

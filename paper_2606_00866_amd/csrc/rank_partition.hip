@@ -685,6 +685,7 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     const uint32_t idx_out = (uint32_t)((exB >> 32) & 0xFFFFu), idx_in = (uint32_t)(exB >> 48);
     if (catv[it] == MORI_CAT_OUT) {
       const uint32_t pg = (uint32_t)(exA & 0xFFFFFFFFu);
+      a.ord[p] = idx_out;
       a.out_prog[idx_out] = p;
       a.out_pg_base[idx_out] = pg;
       *host_mirror(a, a.out_prog + idx_out) = p;
@@ -692,6 +693,7 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     }
     if (catv[it] == MORI_CAT_IN) {  // programs promoted from the CPU (or SSD) tier take the first slots (Sec. 4.3.1)
       const uint32_t pg = (uint32_t)(exA >> 32);
+      a.ord[p] = idx_in;
       a.in_prog[idx_in] = p;
       a.in_pg_base[idx_in] = pg;
       *host_mirror(a, a.in_prog + idx_in) = p;

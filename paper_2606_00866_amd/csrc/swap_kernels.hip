@@ -39,7 +39,7 @@ typedef __attribute__((address_space(1))) const uint8_t gcbyte;
 typedef __attribute__((address_space(1))) uint8_t gbyte;
 
 // The plan's tables (program lists, first slots, page lists, host addresses,
-// the summary) are not written while a swap kernel runs, so they are read
+// the unit ranges) are not written while a swap kernel runs, so they are read
 // through the constant address space: wavefront-uniform reads of them become
 // scalar loads, which wait on their own counter instead of behind the copy's
 // outstanding vector loads and stores.
@@ -47,8 +47,8 @@ typedef __attribute__((address_space(4))) const uint32_t cu32;
 typedef __attribute__((address_space(4))) const uint64_t cu64;
 __device__ inline uint32_t ldc(const uint32_t* p, uint64_t i) { return ((cu32*)p)[i]; }
 __device__ inline uint64_t ldc(const uint64_t* p, uint64_t i) { return ((cu64*)p)[i]; }
-__device__ inline const __attribute__((address_space(4))) DevSummary* sumc(const SwapArgs& s) {
-  return (const __attribute__((address_space(4))) DevSummary*)s.sum;
+__device__ inline const __attribute__((address_space(4))) SwapRange* rangec(const SwapArgs& s) {
+  return (const __attribute__((address_space(4))) SwapRange*)s.range;
 }
 
 // Wavefront-uniform values moved to scalar registers.
@@ -61,17 +61,6 @@ __device__ inline uint64_t uniform64(uint64_t x) {
 constexpr uint32_t NT = 1024;
 constexpr uint32_t LONG_VEC = 4;                 // vectors per thread per round for runs of 32 KiB and more
 constexpr uint32_t MAX_RUNS_PER_PASS = NT / 64;  // groups stay whole wavefronts
-
-// Largest a in [0, n) with base[a] <= x.
-__device__ inline uint32_t find_slice(const uint32_t* base, uint32_t n, uint64_t x) {
-  uint32_t lo = 0, hi = n;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (ldc(base, mid) <= x) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
 
 __device__ inline v4u ld16(gcbyte* base, uint32_t i) {
   return __builtin_nontemporal_load((const gv4u*)(base + (i << 4)));
@@ -88,9 +77,10 @@ __device__ inline void st16(gbyte* base, uint32_t i, v4u v) { __builtin_nontempo
 // index past the run is clamped to the run's last vector, so a thread past the
 // end reads that vector and writes the same bytes back to it (one address for
 // the whole wavefront); masking those stores instead measured 1-3% slower on
-// 32 and 72 KiB runs.
-template <uint32_t G, uint32_t U>
-__device__ inline void copy_run(const uint8_t* src_run, uint8_t* dst_run, uint32_t n16, uint32_t t) {
+// 32 and 72 KiB runs.  `between` runs once, while the first round's loads are
+// in flight.
+template <uint32_t G, uint32_t U, typename F>
+__device__ inline void copy_run(const uint8_t* src_run, uint8_t* dst_run, uint32_t n16, uint32_t t, F between) {
   gcbyte* src = (gcbyte*)uniform64((uint64_t)src_run);
   gbyte* dst = (gbyte*)uniform64((uint64_t)dst_run);
   const uint32_t last = n16 - 1;
@@ -98,53 +88,39 @@ __device__ inline void copy_run(const uint8_t* src_run, uint8_t* dst_run, uint32
     v4u v[U];
 #pragma unroll
     for (uint32_t k = 0; k < U; ++k) v[k] = ld16(src, min(c0 + k * G + t, last));
+    if (c0 == 0) between();
 #pragma unroll
     for (uint32_t k = 0; k < U; ++k) st16(dst, min(c0 + k * G + t, last), v[k]);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
 }
 
-// Unit range of this launch; returns false when there is nothing to do.
-template <bool kOut>
-__device__ inline bool unit_range(const SwapArgs& s, uint32_t n, uint64_t* lo, uint64_t* hi) {
-  const uint64_t LC = s.LC;
-  const uint64_t total = (uint64_t)ldc(s.pg_base, n) * LC;
-  const uint64_t nf = sumc(s)->pages_free_before + sumc(s)->pages_dropped;  // slots needing no wait
-  *lo = 0;
-  *hi = total;
-  if (s.staging) {
-    *lo = s.u_begin;
-    *hi = s.u_end < total ? s.u_end : total;
-  } else if (!kOut && s.part == 1) {
-    uint32_t a = 0, b = n;  // number of moving programs whose first slot is below nf
-    while (a < b) {
-      const uint32_t mid = (a + b) >> 1;
-      if (ldc(s.pg_base, mid) < nf) a = mid + 1;
-      else b = mid;
-    }
-    *hi = (uint64_t)ldc(s.pg_base, a) * LC;
-  } else if (!kOut && s.part == 2) {
-    if (ldc(s.pg_base, n) <= nf) return false;  // no slot reaches a page that is free only later
-    *lo = (uint64_t)ldc(s.pg_base, find_slice(s.pg_base, n, nf)) * LC;
-  }
-  return *lo < *hi;
-}
-
 // Decode state of one wavefront group: the moving program of the current unit.
-// A group's units only increase, so the program index only moves forward.
 struct Cursor {
-  uint32_t a;        // program (index into the direction's list)
   uint64_t first;    // its first page index / slot
   uint64_t nb;       // its blocks
   uint64_t u_first;  // its first unit
+  uint64_t u_end;    // its last unit + 1
   uint8_t* side;     // its host buffer (direct mode)
 };
 
-__device__ inline void cursor_set(const SwapArgs& s, Cursor& c, uint32_t a) {
-  c.a = a;
+__device__ inline uint64_t divide(uint64_t x, uint32_t d) {
+  return (x >> 32) == 0 ? (uint32_t)x / d : x / d;  // the usual case: a 32-bit division
+}
+
+// The program of unit u: units [pg_base[a], pg_base[a + 1]) * LC are program
+// a's, so u / LC is one of its page indices / slots, whose list index the plan
+// has written.  Three dependent scalar loads, however many programs lie between
+// a group's units: with 4 KiB runs and programs of a few dozen blocks a grid
+// stride passes about ten programs, and walking the list program by program
+// held the kernels at 2.6 TB/s.
+__device__ inline void cursor_set(const SwapArgs& s, Cursor& c, uint64_t u) {
+  const uint32_t a = ldc(s.ord, divide(u, s.LC));
   c.first = ldc(s.pg_base, a);
-  c.nb = (uint64_t)ldc(s.pg_base, a + 1) - c.first;
+  const uint64_t next = ldc(s.pg_base, a + 1);
+  c.nb = next - c.first;
   c.u_first = c.first * s.LC;
+  c.u_end = next * s.LC;
   c.side = s.staging ? nullptr : reinterpret_cast<uint8_t*>(ldc(s.addr, ldc(s.prog, a)));
 }
 
@@ -153,8 +129,7 @@ __device__ inline void cursor_set(const SwapArgs& s, Cursor& c, uint32_t a) {
 template <bool kOut>
 __device__ inline bool unit_ends(const SwapArgs& s, Cursor& c, uint64_t u, uint64_t u_lo, uint64_t nf,
                                  const uint8_t** src, uint8_t** dst) {
-  // u < the direction's total units, so the cursor stops at its last program
-  while (u >= c.u_first + c.nb * s.LC) cursor_set(s, c, c.a + 1);
+  if (u >= c.u_end) cursor_set(s, c, u);
   const uint64_t rem = u - c.u_first;
   uint64_t q, i;
   if ((rem >> 32) == 0 && (c.nb >> 32) == 0) {  // the usual case: a 32-bit division
@@ -181,10 +156,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void sw
   // concurrently on the other stream.  A swap-in also stops on the swap-out's
   // (ordered before it by the time it writes a page the swap-out reads): it
   // must not overwrite pages whose KV a failed swap-out did not save.
-  if (sumc(s)->error || s.swap_err[0] || (!kOut && s.swap_err[1])) return;
-  const uint32_t n = kOut ? sumc(s)->n_out : sumc(s)->n_in;
-  uint64_t lo, hi;
-  if (n == 0 || !unit_range<kOut>(s, n, &lo, &hi)) return;
+  if (s.swap_err[0] || (!kOut && s.swap_err[1])) return;
+  uint64_t lo = s.u_begin, hi = s.u_end, nf = 0;
+  if (!s.staging) {
+    const auto* r = rangec(s);
+    nf = r->nf;
+    lo = !kOut && s.part == 2 ? r->second_begin : 0;
+    hi = !kOut && s.part == 1 ? r->first_end : r->total;
+  }
   const uint32_t n16 = (uint32_t)(s.run / 16);
   constexpr uint32_t G = NT / PER;  // threads per run, whole wavefronts
   // groups are whole wavefronts, so the group index is wavefront-uniform
@@ -192,20 +171,27 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void sw
   const uint64_t stride = (uint64_t)gridDim.x * PER;
   uint64_t u = lo + (uint64_t)blockIdx.x * PER + grp;
   if (u >= hi) return;  // the group's whole wavefronts leave together
-  const uint64_t nf = sumc(s)->pages_free_before + sumc(s)->pages_dropped;
   Cursor c;
-  cursor_set(s, c, find_slice(s.pg_base, n, u / s.LC));
+  cursor_set(s, c, u);
   const uint8_t* src;
   uint8_t* dst;
   bool ok = unit_ends<kOut>(s, c, u, lo, nf, &src, &dst);
   for (;;) {
-    // decode the next unit first: its loads overlap this unit's copy
+    // The next unit is decoded while this unit's loads are in flight; on long
+    // runs before them, where holding the stores back for the decode costs
+    // more than it hides (6 GiB of 72 KiB runs: 4.24 ms a pass against 4.29).
     const uint64_t un = u + stride;
     const uint8_t* nsrc = nullptr;
     uint8_t* ndst = nullptr;
     const bool more = un < hi;
-    const bool nok = more && unit_ends<kOut>(s, c, un, lo, nf, &nsrc, &ndst);
-    if (ok) copy_run<G, U>(src, dst, n16, t);
+    bool nok = false;
+    auto decode = [&] { nok = more && unit_ends<kOut>(s, c, un, lo, nf, &nsrc, &ndst); };
+    if (!ok || (PER == 1 && U == LONG_VEC)) {
+      decode();
+      if (ok) copy_run<G, U>(src, dst, n16, t, [] {});
+    } else {
+      copy_run<G, U>(src, dst, n16, t, decode);
+    }
     if (!more) break;
     u = un;
     src = nsrc;
@@ -221,22 +207,27 @@ struct CopyShape {
 // Between HBM buffers, runs of 2048 vectors (32 KiB) and more: one per
 // workgroup, LONG_VEC vectors per thread per round (a 72 KiB run takes a
 // round of 64 KiB and one of 8 KiB; a 32 KiB run one round, half of it
-// clamped); from 1024 vectors: one per workgroup, one vector per thread per
-// round.  Over the host link (kernel-direct mode), runs of 1024 vectors and
-// more: two per workgroup, one vector per thread per round.  Shorter runs: as
-// many per workgroup (a power of two, at most one per wavefront) as give each
-// thread one vector.  Measured in the full-size pipelined rebalance: between
-// HBM buffers four vectors per thread beat one to three, five and eight on
-// runs of 32 and 72 KiB (one is best on 16 KiB runs); over the host link four
-// or two vectors per thread lose 12% or 7% against one (fewer accesses in
-// flight suit the link's two directions), and two runs per workgroup gain 1%.
+// clamped).  Shorter runs: one round each, as many per workgroup (a power of
+// two, at most one per wavefront) as give each thread two vectors when that
+// comes out even (power-of-two runs), else four; a run within one wavefront's
+// 64 lanes one.  One vector per thread keeps too little in flight there: a
+// pair of rebalances of 1.5 GiB takes 1.43 ms with one, 1.25 with two on
+// 4 KiB runs, 1.87 with one, 1.26 with four on 10.25 KiB runs, 1.55 and 1.24
+// on 18 KiB runs.  Over the host link (kernel-direct mode), runs of 1024
+// vectors and more: two per workgroup, one vector per thread per round;
+// shorter ones one vector per thread.  Measured in the full-size pipelined
+// rebalance: between HBM buffers four vectors per thread beat one to three,
+// five and eight on runs of 32 and 72 KiB; over the host link four or two
+// vectors per thread lose 12% or 7% against one (fewer accesses in flight suit
+// the link's two directions), and two runs per workgroup gain 1%.
 CopyShape copy_shape(uint64_t run, bool host_link) {
   const uint64_t n16 = run / 16;
   if (host_link && n16 >= NT) return {2, 1};
-  if (n16 >= 2 * NT) return {1, LONG_VEC};
+  if (!host_link && n16 >= 2 * NT) return {1, LONG_VEC};
+  const uint32_t vec = host_link || n16 <= 64 ? 1 : n16 <= 128 || (n16 & (n16 - 1)) == 0 ? 2 : 4;
   uint32_t per = 1;
-  while (per < MAX_RUNS_PER_PASS && 2ull * per * n16 <= (uint64_t)NT) per *= 2;
-  return {per, 1};
+  while (per < MAX_RUNS_PER_PASS && 2ull * per * n16 <= (uint64_t)NT * vec) per *= 2;
+  return {per, vec};
 }
 
 template <bool kOut, uint32_t PER, uint32_t U>
@@ -244,23 +235,34 @@ void launch_shape(const SwapArgs& a, uint32_t grid, hipStream_t s) {
   hipLaunchKernelGGL((swap_kernel<kOut, PER, U>), dim3(grid), dim3(NT), 0, s, a);
 }
 
+template <bool kOut, uint32_t PER>
+void launch_per(uint32_t vec, const SwapArgs& a, uint32_t grid, hipStream_t s) {
+  switch (vec) {
+    case 1: launch_shape<kOut, PER, 1>(a, grid, s); break;
+    case 2: launch_shape<kOut, PER, 2>(a, grid, s); break;
+    default: launch_shape<kOut, PER, 4>(a, grid, s); break;
+  }
+}
+
 template <bool kOut>
 hipError_t launch_swap(const SwapArgs& a, uint32_t grid, hipStream_t s) {
   const CopyShape sh = copy_shape(a.run, a.host_link != 0);
   switch (sh.per) {
     case 1:
-      if (sh.vec == LONG_VEC) launch_shape<kOut, 1, LONG_VEC>(a, grid, s);
-      else launch_shape<kOut, 1, 1>(a, grid, s);
+      if (sh.vec == 1) launch_shape<kOut, 1, 1>(a, grid, s);
+      else launch_shape<kOut, 1, LONG_VEC>(a, grid, s);
       break;
-    case 2: launch_shape<kOut, 2, 1>(a, grid, s); break;
-    case 4: launch_shape<kOut, 4, 1>(a, grid, s); break;
-    case 8: launch_shape<kOut, 8, 1>(a, grid, s); break;
-    default: launch_shape<kOut, 16, 1>(a, grid, s); break;
+    case 2: launch_per<kOut, 2>(sh.vec, a, grid, s); break;
+    case 4: launch_per<kOut, 4>(sh.vec, a, grid, s); break;
+    case 8: launch_per<kOut, 8>(sh.vec, a, grid, s); break;
+    default: launch_per<kOut, 16>(sh.vec, a, grid, s); break;
   }
   return hipGetLastError();
 }
 
 }  // namespace
+
+uint32_t swap_runs_per_workgroup(uint64_t run, bool host_link) { return copy_shape(run, host_link).per; }
 
 hipError_t launch_swap_out(const SwapArgs& a, uint32_t grid, hipStream_t s) { return launch_swap<true>(a, grid, s); }
 
