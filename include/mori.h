@@ -82,8 +82,7 @@ extern "C" {
 #define MORI_DEV_HOST_ADDR 0x200u     /* swap address not 16-B aligned or outside registered memory */
 #define MORI_DEV_BAD_BLOCK 0x400u     /* eviction order: type label > 2 or last access >= 2^62 */
 #define MORI_DEV_BAD_STATUS 0x800u    /* incremental policy: status value > 2 */
-#define MORI_DEV_STALL 0x1000u        /* eviction order: a sort pass waited too long on another
-                                         workgroup (not expected; the result is not valid) */
+#define MORI_DEV_STALL 0x1000u        /* reserved (no kernel waits for another workgroup) */
 /* classes: program data = 0x00F and 0x800, pool state = 0x0F0, capacity = 0x100, swap = 0x200,
    blocks = 0x400 */
 
@@ -349,7 +348,7 @@ typedef struct {
 } mori_blocks;
 
 /* Bytes of device workspace mori_evict_order needs for num_blocks blocks
- * (about 36 bytes per block, plus 1 MiB). */
+ * (about 33 bytes per block, plus 1 MiB). */
 int mori_evict_workspace(uint32_t num_blocks, uint64_t* bytes);
 
 /* Eviction order of one tier (MORI_TIER_GPU or MORI_TIER_CPU), enqueued on
@@ -369,7 +368,7 @@ int mori_evict_order(const mori_blocks* blocks, uint32_t tier, uint64_t need_byt
  * workspace in a device array the library holds on each GPU for the life of
  * the process, instead of a caller buffer.  Same result for the same input;
  * at most MORI_EVICT_NOALLOC_MAX_BLOCKS blocks (ENOSPC above; the array is
- * about 19.5 MiB per GPU).  Nothing is allocated: the array's device address
+ * about 17.5 MiB per GPU).  Nothing is allocated: the array's device address
  * is looked up on the first call on each GPU (call it once before a capture
  * starts), and each call enqueues kernels only, which clear what must start
  * at zero.  Every call on one GPU uses the same array: calls whose work

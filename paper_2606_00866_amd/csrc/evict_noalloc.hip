@@ -17,10 +17,6 @@ namespace {
 constexpr uint64_t kScratchBytes = evict_workspace_bytes(MORI_EVICT_NOALLOC_MAX_BLOCKS);
 static_assert(kScratchBytes % 256 == 0, "workspace pieces are 256-B aligned");
 
-// The workspace is largest at the maximum: the 4-keys-per-thread tiles are used up
-// to 2^19 blocks, and every piece grows with N at a fixed tile size.
-static_assert(MORI_EVICT_NOALLOC_MAX_BLOCKS <= EVICT_SMALL_SORT, "one tile size up to the maximum");
-
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;

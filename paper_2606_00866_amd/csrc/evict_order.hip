@@ -5,47 +5,45 @@
 // type first, in tier-reversed order (GPU: inactive, idle, busy; CPU:
 // inactive, busy, idle), least recently used first within a type, equal
 // (type, time) lowest block id first.  That is one ascending sort of the
-// 64-bit key (type position << 62 | last access) with the block id riding
-// along, done here as a device-wide stable LSD radix sort:
+// 64-bit key (type position << 62 | last access), equal keys by block id,
+// followed by the bytes freed along that order and the number of evictions
+// that frees the requested bytes.  The pair (key, id) is unique, so any way of
+// sorting gives the same order.  Three forms by block count, each bound by the
+// latency of its chain of launches rather than by bandwidth (a call reads and
+// writes 25 B a block):
 //
-//   keys     build keys, validate, OR/AND of all keys; for the one-kernel
-//            passes also the digit counts of all eight passes at once (they
-//            do not depend on the order), one set per workgroup, equal keys
-//            (the blocks of a program share their time) counted once per run;
-//   totals   those counts summed over the keys workgroups;
-//   per pass (8-bit digit, 8 passes; a digit on which every key agrees needs
-//   no pass, and each kernel works out from the OR/AND which of the two
-//   key/value buffers holds the current order, so such a pass is empty
-//   launches and no memory traffic), one workgroup per tile, in one of two
-//   forms by tile count:
-//     one kernel (up to ONESWEEP_TILES tiles):
-//     - the tile index comes from a counter in the order workgroups start, so
-//       every lower tile belongs to a workgroup that is already running;
-//     - the stable rank of every key among the tile's keys of its digit:
-//       wave64 ballots over the 8 digit bits rank it within its wave's 64
-//       keys of a slice, one scan per digit over (slice, wave) in LDS orders
-//       the groups as the keys were ordered;
-//     - the tile's count of each digit is published, then the keys of that
-//       digit in all lower tiles are summed by looking back over the
-//       published counts, four tiles per round, until a tile that already
-//       holds its inclusive sum (a decoupled look-back; the wait is bounded
-//       and reports a stall);
-//     - position = digit base (a 256-entry scan of the digit totals) + keys
-//       of the digit in lower tiles + the rank in the tile;
-//     three kernels (more tiles):
+//   direct  (up to DIRECT_MAX) one kernel: every workgroup stages all keys in
+//           LDS and each wave counts, for its blocks, the blocks before it and
+//           their bytes, which are the block's place and its prefix; no
+//           workgroup waits for another.
+//   buckets (up to BUCKET_MAX) four kernels: a sorted sample gives up to 1024
+//           buckets of about equal size whatever the keys' distribution and
+//           ties; the blocks of each bucket are counted, gathered and sorted
+//           in LDS by one workgroup, which knows from the bucket totals where
+//           its bucket begins.
+//   radix   (above) a device-wide stable LSD radix sort:
+//     keys     build keys, validate, OR/AND of all keys;
+//     per pass (8-bit digit, 8 passes; a digit on which every key agrees needs
+//     no pass, and each kernel works out from the OR/AND which of the two
+//     key/value buffers holds the current order, so such a pass is empty
+//     launches and no memory traffic), one workgroup per tile:
 //     - hist: per tile, a 256-bin histogram -> hist[digit][tile];
 //     - dscan: one workgroup per digit, an exclusive scan of that digit's
 //       counts over the tiles and the digit's total;
-//     - scatter: the same ranking and position, with the lower tiles' count
-//       read from the scanned histogram;
-//   prefix   inclusive u64 scan of block bytes in eviction order (tile scans,
-//            then a fix-up whose workgroups each sum the tile totals below
-//            their tile, or above FIX_SCAN_TILES a one-workgroup scan of the
-//            tile totals first) and the number of evictions that frees the
-//            requested bytes.
+//     - scatter: the stable rank of every key among the tile's keys of its
+//       digit (wave64 ballots over the 8 digit bits rank it within its wave's
+//       64 keys of a slice, one scan per digit over (slice, wave) in LDS orders
+//       the groups as the keys were ordered); position = digit base + keys of
+//       the digit in lower tiles + that rank;
+//     prefix   inclusive u64 scan of block bytes in eviction order (tile scans,
+//              then a fix-up whose workgroups each sum the tile totals below
+//              their tile, or above FIX_SCAN_TILES a one-workgroup scan of the
+//              tile totals first) and the eviction count.
 //
-// Everything is latency-bound at 10^5-10^6 blocks (tens of microseconds);
-// the workspace is the caller's, so nothing is allocated here.
+// The workspace is the caller's, so nothing is allocated here.
+#include <algorithm>
+#include <type_traits>
+
 #include "mori_internal.h"
 #include "wave.h"
 
@@ -54,26 +52,42 @@ namespace {
 
 constexpr int ET = EVICT_WG;            // threads per tile workgroup
 constexpr int ENW = ET / 64;            // waves per tile workgroup
-// Keys per thread (tile = 256 x that), measured with the bench's block metadata.
-inline int keys_per_thread(uint32_t N) { return evict_keys_per_thread(N); }
+constexpr int EIPT = EVICT_KEYS_PER_THREAD;  // keys per thread of a radix tile (measured against 4)
 constexpr uint64_t TIME_LIMIT = 1ull << 62;
-constexpr uint32_t KEY_WG_MAX = EVICT_KEY_WG_MAX;  // workgroups of the keys kernel at most (one digit-count set each)
-// Keys per thread whose loads the keys kernel issues together: 4 for the
-// look-back passes, 8 above (measured: 8 and 16 are 3 and 11 us slower at
-// 69 938 blocks, 8 is 2.5 us faster at 2^20).
-constexpr int KEYS_PER_ROUND_SMALL = 4, KEYS_PER_ROUND_LARGE = 8;
-constexpr uint32_t TOT_SPLIT = 8;        // totals: workgroups per pass, each summing a share of the sets
-// Tile counts up to this use one look-back kernel per pass, more use three
-// kernels (histogram, per-digit scan, scatter): each look-back round is a
-// device-coherent load, so the look-back chains grow with the tile count.
-constexpr uint32_t ONESWEEP_TILES = 128;
+constexpr uint32_t KEY_WG_MAX = 128;    // workgroups of the keys kernel at most (more: same-address atomics)
+constexpr int KEYS_PER_ROUND = 8;       // keys per thread whose loads the keys kernel issues together
 // Tile counts up to this finish the prefix with one kernel (every workgroup
 // reads the tile totals: 8 B each) instead of a tile scan, a fix-up and a
 // result kernel.
 constexpr uint32_t FIX_SCAN_TILES = 1024;
-constexpr uint64_t ST_AGG = 1ull << 32;  // status flags: the tile's own count ...
-constexpr uint64_t ST_INCL = 2ull << 32; // ... or its inclusive count over tiles 0..t
-constexpr uint32_t SPIN_LIMIT = 1u << 22;  // polls of one status word before reporting a stall
+
+// Direct and bucket forms: workgroups of 1024 threads.  Measured per call
+// (sizes given, half the blocks tied), the form before -> this one:
+//   blocks     4 096   8 192   16 384   69 938   262 144   2^20
+//   us         60->8   66->15  70->22   86->27   114->36   178->67
+// Direct counting grows with the square: 15.3 us at 8 192 blocks against 21 for
+// the buckets, about 24 at 10 240, and the keys no longer fit LDS twice as far.
+constexpr int BT = 1024, BNW = BT / 64;
+constexpr uint32_t DIRECT_MAX = 8192;
+constexpr uint32_t DIRECT_WG = 256;         // one per compute unit
+// The bucket form ends where packed entries run out of id bits and buckets of
+// the smallest count outgrow LDS.
+constexpr uint32_t BUCKET_ID_BITS = 20;
+constexpr uint32_t BUCKET_MAX = 1u << BUCKET_ID_BITS;
+constexpr uint32_t BUCKETS_MAX = 1024;
+// Eight samples a bucket, at least 1024 (more balance the buckets better, but
+// ranking them grows with the square: 4096 for 256 buckets 1.5 us slower).
+constexpr uint32_t SAMPLES_PER_BUCKET = 8, SAMPLES_MIN = 1024;
+constexpr uint32_t SAMPLES_MAX = SAMPLES_PER_BUCKET * BUCKETS_MAX;
+constexpr int SAMPLE_WG = 64;
+// Blocks per bucket aimed at while there are buckets left: 1024 is 9 us slower
+// at 131 072 blocks and 5 us at 2^19, 256 within 3 us either way.
+constexpr uint32_t BUCKET_AVG = 512;
+constexpr int BUCKET_IPT = 6;               // a bucket of up to 6144 blocks is sorted in LDS
+constexpr uint32_t BUCKET_CAP = BT * BUCKET_IPT;
+// Blocks per thread of the partition kernels: one while that leaves a workgroup
+// for each compute unit, two above (2^20 blocks: 2 us faster than one or four).
+constexpr uint32_t PARTITION_ONE_MAX = 1u << 18;
 
 struct EvictArgs {
   uint32_t N, ntiles, tier;
@@ -83,14 +97,8 @@ struct EvictArgs {
   uint64_t unit_bytes, need;
   uint64_t* keys[2];
   uint32_t* vals[2];
-  uint32_t* hist;       // [256][ntiles] (three-kernel passes)
-  uint32_t* dtot;       // [256] keys per digit (three-kernel passes)
-  uint32_t onesweep;    // passes are single look-back kernels (few tiles)
-  uint64_t* status[2];  // [ntiles][256] per pass: (flag << 32) | count; passes alternate the two
-  uint32_t* part;       // [key_wg][8][256] digit counts of each keys workgroup, all passes
-  uint32_t* gtot;       // [8][256] keys per digit, all passes
-  uint32_t key_wg;      // workgroups of the keys kernel
-  uint32_t* tile_ctr;   // [8] tiles taken in each pass
+  uint32_t* hist;       // [256][ntiles]
+  uint32_t* dtot;       // [256] keys per digit
   uint64_t* tile_sum;   // [ntiles]
   uint64_t* misc;       // [0] OR of keys, [1] AND of keys, [2] error bits, [3] evictions short of need
   uint32_t* order;      // out [N]
@@ -98,35 +106,28 @@ struct EvictArgs {
   uint32_t* result;     // out [2]: count, error bits
 };
 
-__global__ __launch_bounds__(ET) void evict_init_kernel(EvictArgs a) {
-  // status of the first pass that runs, and the tile counters
-  for (uint64_t i = (uint64_t)blockIdx.x * ET + threadIdx.x; i < (uint64_t)a.ntiles * 256; i += (uint64_t)gridDim.x * ET)
-    a.status[0][i] = 0;
-  for (uint32_t i = blockIdx.x * ET + threadIdx.x; i < 8 * 256; i += gridDim.x * ET) a.gtot[i] = 0;
-  if (blockIdx.x == 0) {
-    if (threadIdx.x < 8) a.tile_ctr[threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
-      a.misc[0] = 0;
-      a.misc[1] = ~0ull;
-      a.misc[2] = 0;
-      a.misc[3] = 0;
-    }
-  }
+// A block's key; invalid metadata (reported separately) gives some key.
+__device__ inline uint64_t block_key(uint32_t tier, uint32_t type, uint64_t last_access) {
+  // position of each type label in the tier's eviction order: GPU inactive,
+  // idle, busy; CPU inactive, busy, idle
+  const uint32_t pos = tier == MORI_TIER_GPU ? 2u - min(type, 2u) : type == MORI_TYPE_BUSY ? 1u
+                       : type == MORI_TYPE_IDLE ? 2u : 0u;
+  return ((uint64_t)pos << 62) | (last_access & (TIME_LIMIT - 1));
+}
+__device__ inline uint64_t block_error(uint32_t type, uint64_t last_access) {
+  return type > MORI_TYPE_INACTIVE || last_access >= TIME_LIMIT ? MORI_DEV_BAD_BLOCK : 0u;
 }
 
-template <int KEYS_PER_ROUND>
+__global__ void evict_init_kernel(EvictArgs a) {
+  a.misc[0] = 0;
+  a.misc[1] = ~0ull;
+  a.misc[2] = 0;
+  a.misc[3] = 0;
+}
+
 __global__ __launch_bounds__(ET) void evict_keys_kernel(EvictArgs a) {
-  // position of each type label in the tier's eviction order (busy, idle, inactive)
-  const uint32_t gpu_pos[3] = {2, 1, 0}, cpu_pos[3] = {1, 2, 0};
-  const uint32_t* pos = a.tier == MORI_TIER_GPU ? gpu_pos : cpu_pos;
-  __shared__ uint32_t s_c[8][256];  // this workgroup's keys per (pass, digit)
-#pragma unroll
-  for (int k = 0; k < 8; ++k) s_c[k][threadIdx.x] = 0;
-  __syncthreads();
   uint64_t o = 0, n = ~0ull, err = 0;
-  const int lane = threadIdx.x & 63;
-  // rounds of KEYS_PER_ROUND keys per thread, all their loads issued first;
-  // uniform trip count: the cross-lane steps below need every lane of the wave
+  // rounds of KEYS_PER_ROUND keys per thread, all their loads issued first
   for (uint64_t i0 = (uint64_t)blockIdx.x * ET * KEYS_PER_ROUND; i0 < a.N;
        i0 += (uint64_t)gridDim.x * ET * KEYS_PER_ROUND) {
     uint8_t typ[KEYS_PER_ROUND];
@@ -140,54 +141,15 @@ __global__ __launch_bounds__(ET) void evict_keys_kernel(EvictArgs a) {
 #pragma unroll
     for (int u = 0; u < KEYS_PER_ROUND; ++u) {
       const uint64_t i = i0 + (uint64_t)u * ET + threadIdx.x;
-      bool valid = i < a.N;
-      uint64_t key = 0;
-      if (valid) {
-        if (typ[u] > MORI_TYPE_INACTIVE || la[u] >= TIME_LIMIT) {
-          err |= MORI_DEV_BAD_BLOCK;
-          valid = false;
-        } else {
-          key = ((uint64_t)pos[typ[u]] << 62) | la[u];
-          a.keys[0][i] = key;
-          a.vals[0][i] = (uint32_t)i;
-          o |= key;
-          n &= key;
-        }
-      }
-      if (!a.onesweep) continue;  // uniform: the three-kernel passes count per tile
-      // runs of equal keys within the wave (the blocks of a program share their
-      // time): the first lane of a run adds the run's length for each digit
-      const uint64_t prev = __shfl_up(key, 1, 64);
-      const bool prev_valid = __shfl_up(valid ? 1 : 0, 1, 64) != 0;
-      const bool head = valid && (lane == 0 || !prev_valid || prev != key);
-      const uint64_t heads = __ballot(head);
-      const uint64_t vmask = __ballot(valid);
-      if (!heads) continue;  // uniform: no valid key in this wave
-      const uint64_t ends = heads | ~vmask;  // a run ends at the next head or invalid lane
-      uint32_t len = 0;
-      if (head) {
-        const uint64_t later = lane == 63 ? 0ull : ends & ~((2ull << lane) - 1ull);
-        len = (later ? (uint32_t)__builtin_ctzll(later) : 64u) - (uint32_t)lane;
-      }
-      // a digit that every run of the wave shares (the high time digits and
-      // the type, mostly) takes one increment of all the wave's valid keys
-      const int first = __builtin_ctzll(heads);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const uint32_t d = (uint32_t)(key >> (8 * k)) & 255u;
-        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
-        if (__ballot(head && d != d0) == 0) {
-          if (lane == first) atomicAdd(&s_c[k][d0], (uint32_t)__popcll(vmask));
-        } else if (head) {
-          atomicAdd(&s_c[k][d], len);
-        }
-      }
+      if (i >= a.N) continue;
+      err |= block_error(typ[u], la[u]);
+      const uint64_t key = block_key(a.tier, typ[u], la[u]);
+      a.keys[0][i] = key;
+      a.vals[0][i] = (uint32_t)i;
+      o |= key;
+      n &= key;
     }
   }
-  __syncthreads();
-  if (a.onesweep)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) a.part[((uint64_t)blockIdx.x * 8 + k) * 256 + threadIdx.x] = s_c[k][threadIdx.x];
   // wave, then workgroup reduction: one set of global atomics per workgroup
   __shared__ uint64_t s_red[3][ENW];
   o = wave::all_or<uint64_t>(o);
@@ -227,7 +189,6 @@ __device__ inline int source_buffer(const EvictArgs& a, int shift) {
   return n & 1;
 }
 
-template <int EIPT>
 __global__ __launch_bounds__(ET) void evict_hist_kernel(EvictArgs a, int shift) {
   __shared__ uint32_t s_h[256];
   if (a.misc[2] || !digit_varies(a, shift)) return;
@@ -273,7 +234,6 @@ __device__ inline uint32_t scan256(uint32_t v, uint32_t* s_w, uint32_t* total) {
 // s_tstart[d]: first tile-local slot of digit d; s_off[d]: its global slot;
 // s_cnt: the (slice, wave, digit) offsets within each digit; n: valid keys.
 // Every thread calls it; it begins and ends with a barrier.
-template <int EIPT>
 __device__ void store_tile(const uint64_t (&key)[EIPT], const uint32_t (&val)[EIPT], const uint32_t (&dig)[EIPT],
                            const uint32_t (&rnk)[EIPT], const uint16_t (*s_cnt)[ENW][256], const uint32_t* s_tstart,
                            const uint32_t* s_off, uint64_t* s_k, uint32_t* s_v, uint32_t n, int shift, uint64_t* kd,
@@ -321,7 +281,6 @@ __global__ __launch_bounds__(ET) void evict_dscan_kernel(EvictArgs a, int shift)
   if (threadIdx.x == 0) a.dtot[blockIdx.x] = carry;
 }
 
-template <int EIPT>
 __global__ __launch_bounds__(ET) void evict_scatter_kernel(EvictArgs a, int shift) {
   // s_cnt[slice][wave][digit]: keys of that digit in that wave's 64 keys of the
   // slice, then (after the per-digit scan) their offset within the tile
@@ -378,147 +337,12 @@ __global__ __launch_bounds__(ET) void evict_scatter_kernel(EvictArgs a, int shif
     }
   uint32_t n;
   s_tstart[tid] = scan256(run, s_w, &n);
-  store_tile<EIPT>(key, val, dig, rnk, s_cnt, s_tstart, s_off, s_k, s_v, n, shift, kd, vd);
-}
-
-// Keys per digit of every pass: workgroup (pass, share) sums a share of the
-// keys workgroups' counts, one digit per thread.
-__global__ __launch_bounds__(ET) void evict_totals_kernel(EvictArgs a) {
-  const uint32_t k = blockIdx.x / TOT_SPLIT, j = blockIdx.x % TOT_SPLIT;
-  uint32_t sum = 0;
-  for (uint32_t g = j; g < a.key_wg; g += TOT_SPLIT) sum += a.part[((uint64_t)g * 8 + k) * 256 + threadIdx.x];
-  if (sum) atomicAdd(&a.gtot[k * 256 + threadIdx.x], sum);
-}
-
-__device__ inline void status_store(uint64_t* p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline uint64_t status_load(const uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// One pass of the sort (the digit at `shift`), one workgroup per tile.
-template <int EIPT>
-__global__ __launch_bounds__(ET) void evict_pass_kernel(EvictArgs a, int shift) {
-  // s_cnt[slice][wave][digit]: keys of that digit in that wave's 64 keys of the
-  // slice, then (after the per-digit scan) their offset within the tile
-  __shared__ uint16_t s_cnt[EIPT][ENW][256];
-  __shared__ uint32_t s_off[256];  // this tile's global base per digit
-  __shared__ uint32_t s_w[ENW];
-  __shared__ uint32_t s_tile;
-  if (a.misc[2] || !digit_varies(a, shift)) return;
-  const int src = source_buffer(a, shift);  // the parity of this pass among those that run
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  if (tid == 0) s_tile = atomicAdd(&a.tile_ctr[shift >> 3], 1u);
-#pragma unroll
-  for (int it = 0; it < EIPT; ++it)
-#pragma unroll
-    for (int w = 0; w < ENW; ++w) s_cnt[it][w][tid] = 0;
-  const uint32_t total_d = a.gtot[(shift >> 3) * 256 + tid];  // keys of this digit in all tiles
-  __syncthreads();
-  const uint32_t tile = s_tile;
-  // the next pass that runs uses the other status array; the previous one that
-  // used it has finished
-  a.status[src ^ 1][(uint64_t)tile * 256 + tid] = 0;
-  const uint64_t* ks = a.keys[src];
-  const uint32_t* vs = a.vals[src];
-  uint64_t* kd = a.keys[src ^ 1];
-  uint32_t* vd = a.vals[src ^ 1];
-  const uint64_t base = (uint64_t)tile * (ET * EIPT);
-  // rank of every key among the keys of its digit in its wave's slice (ballots)
-  const uint64_t lanemask_lt = (1ull << lane) - 1ull;
-  uint64_t key[EIPT];
-  uint32_t val[EIPT], dig[EIPT], rnk[EIPT];
-#pragma unroll
-  for (int it = 0; it < EIPT; ++it) {
-    const uint64_t i = base + it * ET + tid;
-    const bool valid = i < a.N;
-    key[it] = valid ? ks[i] : 0ull;
-    val[it] = valid ? vs[i] : 0u;
-    const uint32_t d = (uint32_t)(key[it] >> shift) & 255u;
-    const uint64_t same = __ballot(valid) & ~wave::digit_differs<8>(d);
-    const uint32_t r = __popcll(same & lanemask_lt);
-    if (valid && r == 0) s_cnt[it][wid][d] = (uint16_t)__popcll(same);
-    dig[it] = valid ? d : 256u;
-    rnk[it] = r;
-  }
-  __syncthreads();
-  // per digit (one per thread): offsets in (slice, wave) order, i.e. original
-  // key order, and the tile's count of the digit
-  uint32_t run = 0;
-#pragma unroll
-  for (int it = 0; it < EIPT; ++it)
-#pragma unroll
-    for (int w = 0; w < ENW; ++w) {
-      const uint32_t c = s_cnt[it][w][tid];
-      s_cnt[it][w][tid] = (uint16_t)run;
-      run += c;
-    }
-  // publish, then look back over the lower tiles
-  uint64_t* st = a.status[src];
-  uint64_t* mine = st + (uint64_t)tile * 256 + tid;
-  uint32_t before = 0;
-  if (tile == 0) {
-    status_store(mine, ST_INCL | run);
-  } else {
-    status_store(mine, ST_AGG | run);
-    // rounds of four tiles below the next unaccounted one, loaded at once and
-    // taken in order: counts add up until a tile holding its inclusive sum; a
-    // tile that has not published yet ends the round and is polled again
-    constexpr int LB = 4;  // measured: 2 and 4 alike, 8 1-2 us slower, 16 15-20 us slower
-    uint32_t next = tile;  // tiles next..tile-1 are accounted for
-    uint32_t spins = 0;
-    bool done = false;
-    while (!done) {
-      uint64_t w[LB];
-#pragma unroll
-      for (int j = 0; j < LB; ++j)
-        w[j] = next > (uint32_t)j ? status_load(st + (uint64_t)(next - 1 - j) * 256 + tid) : ST_INCL;
-      int used = 0;
-#pragma unroll
-      for (int j = 0; j < LB; ++j) {
-        if (used < j) break;  // an earlier entry of this round was not ready
-        const uint64_t flag = w[j] >> 32;
-        if (flag == 0) break;
-        before += (uint32_t)w[j];
-        used = j + 1;
-        if (flag == (ST_INCL >> 32)) {
-          done = true;
-          break;
-        }
-      }
-      next -= (uint32_t)used;
-      if (!done && used < LB) {  // the tile below `next` has not published yet
-        if (++spins > SPIN_LIMIT) {
-          atomicOr((unsigned long long*)&a.misc[2], (unsigned long long)MORI_DEV_STALL);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-    status_store(mine, ST_INCL | (uint64_t)(before + run));
-  }
-  // stores straight from registers: at up to 128 tiles, staging them through
-  // LDS in digit order (as the three-kernel scatter does) measured slower
-  uint32_t tot;
-  const uint32_t digit_base = scan256(total_d, s_w, &tot);
-  s_off[tid] = digit_base + before;
-  __syncthreads();
-#pragma unroll
-  for (int it = 0; it < EIPT; ++it) {
-    const uint32_t d = dig[it];
-    if (d < 256u) {
-      const uint32_t pos = s_off[d] + s_cnt[it][wid][d] + rnk[it];
-      kd[pos] = key[it];
-      vd[pos] = val[it];
-    }
-  }
+  store_tile(key, val, dig, rnk, s_cnt, s_tstart, s_off, s_k, s_v, n, shift, kd, vd);
 }
 
 // Inclusive scan of freed bytes within each tile; tile totals to tile_sum.
 // Global memory is read and written in striped (coalesced) order and the
 // blocked per-thread scan runs on an LDS copy of the tile.
-template <int EIPT>
 __global__ __launch_bounds__(ET) void evict_prefix_tiles_kernel(EvictArgs a) {
   __shared__ uint64_t s_b[ET * EIPT];
   __shared__ uint64_t s_w[ENW + 1];
@@ -596,7 +420,6 @@ __global__ __launch_bounds__(1024) void evict_prefix_top_kernel(EvictArgs a) {
   }
 }
 
-template <int EIPT>
 __global__ __launch_bounds__(ET) void evict_prefix_fix_kernel(EvictArgs a) {
   if (a.misc[2]) return;
   const uint64_t add = a.tile_sum[blockIdx.x];
@@ -627,7 +450,6 @@ __global__ __launch_bounds__(ET) void evict_prefix_fix_kernel(EvictArgs a) {
 // decreases, so that tile is unique; without one, the last tile's workgroup
 // reports every block), so neither the one-workgroup tile scan nor the result
 // kernel runs.
-template <int EIPT>
 __global__ __launch_bounds__(ET) void evict_prefix_fix_scan_kernel(EvictArgs a) {
   __shared__ uint64_t s_red[ENW][2];
   if (a.misc[2]) {
@@ -697,45 +519,591 @@ __global__ void evict_result_kernel(EvictArgs a) {
   a.result[1] = (uint32_t)err;
 }
 
-template <int EIPT>
-void launch_tiles(const EvictArgs& a, hipStream_t s) {
-  for (int shift = 0; shift < 64; shift += 8) {
-    if (a.onesweep) {
-      hipLaunchKernelGGL(evict_pass_kernel<EIPT>, dim3(a.ntiles), dim3(ET), 0, s, a, shift);
-    } else {
-      hipLaunchKernelGGL(evict_hist_kernel<EIPT>, dim3(a.ntiles), dim3(ET), 0, s, a, shift);
-      hipLaunchKernelGGL(evict_dscan_kernel, dim3(256), dim3(ET), 0, s, a, shift);
-      hipLaunchKernelGGL(evict_scatter_kernel<EIPT>, dim3(a.ntiles), dim3(ET), 0, s, a, shift);
-    }
+// ---- direct and bucket forms ------------------------------------------------
+
+__device__ inline uint64_t uniform64(uint64_t x) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+}
+
+// For E consecutive staged elements i0 .. i0 + E - 1 of one wave (i0 a multiple
+// of E): how many staged keys come before each (lower key, or equal key and
+// lower index) and with BYTES the sum of their sizes.  The keys come in chunks
+// of 64, a multiple of GROUP of them; keys past the last element are all ones.
+// The elements' keys are uniform, so a chunk costs a 64-bit compare against a
+// scalar and an add of the carry per element.  Equal keys come first in lower
+// groups of chunks, where the compare is with key + 1, not in higher ones,
+// where it is with the key, and by index in the elements' own group.
+constexpr uint32_t GROUP = 4;  // chunks whose loads are in flight together
+template <int E, bool BYTES>
+__device__ inline void count_before(const uint64_t* s_key, const uint32_t* s_size, uint32_t chunks, uint32_t i0,
+                                    uint32_t (&rank)[E], uint64_t (&bytes)[E]) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint64_t k[E], sum[E];
+  uint32_t cnt[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    k[e] = uniform64(s_key[i0 + e]);
+    cnt[e] = 0;
+    sum[e] = 0;
   }
-  hipLaunchKernelGGL(evict_prefix_tiles_kernel<EIPT>, dim3(a.ntiles), dim3(ET), 0, s, a);
-  if (a.ntiles <= FIX_SCAN_TILES) {
-    hipLaunchKernelGGL(evict_prefix_fix_scan_kernel<EIPT>, dim3(a.ntiles), dim3(ET), 0, s, a);
-  } else {
-    hipLaunchKernelGGL(evict_prefix_top_kernel, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(evict_prefix_fix_kernel<EIPT>, dim3(a.ntiles), dim3(ET), 0, s, a);
-    hipLaunchKernelGGL(evict_result_kernel, dim3(1), dim3(1), 0, s, a);
+  auto group = [&](uint32_t c0, auto limit) {
+    uint64_t kj[GROUP];
+    uint32_t sz[GROUP];
+#pragma unroll
+    for (uint32_t g = 0; g < GROUP; ++g) {
+      kj[g] = s_key[(c0 + g) * 64 + lane];
+      sz[g] = BYTES ? s_size[(c0 + g) * 64 + lane] : 0u;
+    }
+#pragma unroll
+    for (uint32_t g = 0; g < GROUP; ++g)
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const bool before = kj[g] < limit(e, (c0 + g) * 64 + lane);
+        cnt[e] += before;
+        if (BYTES) sum[e] += before ? sz[g] : 0u;
+      }
+  };
+  const uint32_t own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(i0 / (64 * GROUP) * GROUP));
+  for (uint32_t c = 0; c < own; c += GROUP) group(c, [&](int e, uint32_t) { return k[e] + 1; });
+  group(own, [&](int e, uint32_t j) { return k[e] + (j < i0 + e); });
+  for (uint32_t c = own + GROUP; c < chunks; c += GROUP) group(c, [&](int e, uint32_t) { return k[e]; });
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    rank[e] = wave::sum(cnt[e]);
+    bytes[e] = BYTES ? wave::sum(sum[e]) : rank[e];
   }
 }
 
-}  // namespace
+// One block's entry of the order, its prefix (`through` = bytes freed up to and
+// with it) and, where the prefix first reaches need, the eviction count.
+__device__ inline void emit(const EvictArgs& a, uint32_t rank, uint32_t id, uint64_t through, uint64_t own) {
+  a.order[rank] = id;
+  if (a.prefix) a.prefix[rank] = through;
+  if (through >= a.need && through - own < a.need) a.result[0] = rank + 1;
+}
 
-hipError_t launch_evict(uint32_t N, const uint8_t* type, const uint64_t* last_access, const uint32_t* size,
-                        uint64_t unit_bytes, uint32_t tier, uint64_t need, void* workspace, uint32_t* order,
-                        uint64_t* prefix, uint32_t* result, hipStream_t s) {
-  EvictArgs a{};
-  a.N = N;
-  const int kpt = keys_per_thread(N);
-  const uint64_t tile = (uint64_t)ET * kpt;
-  a.ntiles = (uint32_t)(((uint64_t)N + tile - 1) / tile);
-  a.tier = tier;
-  a.type = type;
-  a.last_access = last_access;
-  a.size = size;
-  a.unit_bytes = unit_bytes;
-  a.need = need;
+// The result's words that no block's entry decides.  One thread.
+__device__ inline void finish_result(const EvictArgs& a, uint64_t err, uint64_t total) {
+  a.result[1] = (uint32_t)err;
+  if (err || a.need == 0) a.result[0] = 0;
+  else if (total < a.need) a.result[0] = a.N;
+}
+
+// Up to DIRECT_MAX blocks, one launch.  Counting is quadratic but spread over
+// every compute unit.
+template <bool SIZES, int E>
+__global__ __launch_bounds__(BT) void evict_direct_kernel(EvictArgs a) {
+  __shared__ uint64_t s_key[DIRECT_MAX];
+  __shared__ uint32_t s_size[SIZES ? DIRECT_MAX : 1];
+  __shared__ uint32_t s_err;
+  __shared__ uint64_t s_tot[BNW];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint32_t chunks = (a.N + 64 * GROUP - 1) / (64 * GROUP) * GROUP;
+  if (tid == 0) s_err = 0;
+  __syncthreads();
+  uint64_t err = 0, units = 0;
+  constexpr int U = 4;  // blocks per thread whose loads are in flight together
+  for (uint32_t j0 = tid; j0 < chunks * 64; j0 += U * BT) {
+    uint32_t ty[U], sz[U];
+    uint64_t la[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t j = min(j0 + u * BT, a.N - 1);
+      ty[u] = a.type[j];
+      la[u] = a.last_access[j];
+      sz[u] = SIZES ? a.size[j] : 1u;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t j = j0 + u * BT;
+      if (j >= chunks * 64) break;
+      const bool valid = j < a.N;
+      if (valid) {
+        err |= block_error(ty[u], la[u]);
+        units += sz[u];
+      }
+      s_key[j] = valid ? block_key(a.tier, ty[u], la[u]) : ~0ull;
+      if (SIZES) s_size[j] = valid ? sz[u] : 0u;
+    }
+  }
+  if (err) atomicOr(&s_err, (uint32_t)err);
+  units = wave::sum(units);
+  if (lane == 0) s_tot[wid] = units;
+  __syncthreads();
+  if (blockIdx.x == 0 && tid == 0) {
+    uint64_t total = 0;
+    for (int w = 0; w < BNW; ++w) total += s_tot[w];
+    finish_result(a, s_err, total * a.unit_bytes);
+  }
+  if (s_err) return;
+  const uint32_t waves = gridDim.x * BNW;
+  for (uint32_t i0 = (blockIdx.x * BNW + wid) * E; i0 < a.N; i0 += E * waves) {
+    uint32_t rank[E];
+    uint64_t before[E];
+    count_before<E, SIZES>(s_key, s_size, chunks, i0, rank, before);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (lane == 0 && i0 + e < a.N) {
+        const uint64_t own = SIZES ? s_size[i0 + e] : 1u;
+        emit(a, rank[e], i0 + e, (before[e] + own) * a.unit_bytes, own * a.unit_bytes);
+      }
+  }
+}
+
+__global__ void evict_empty_kernel(EvictArgs a) {
+  a.result[0] = 0;
+  a.result[1] = 0;
+}
+
+void launch_direct(const EvictArgs& a, hipStream_t s) {
+  if (a.N == 0) {
+    hipLaunchKernelGGL(evict_empty_kernel, dim3(1), dim3(1), 0, s, a);
+    return;
+  }
+  const uint32_t wg = (a.N + BNW - 1) / BNW;
+  const dim3 grid(wg < DIRECT_WG ? wg : DIRECT_WG);
+  const bool one = a.N <= DIRECT_WG * BNW;  // one block a wave, else two that share their LDS reads
+  if (a.size && one) hipLaunchKernelGGL((evict_direct_kernel<true, 1>), grid, dim3(BT), 0, s, a);
+  else if (a.size) hipLaunchKernelGGL((evict_direct_kernel<true, 2>), grid, dim3(BT), 0, s, a);
+  else if (one) hipLaunchKernelGGL((evict_direct_kernel<false, 1>), grid, dim3(BT), 0, s, a);
+  else hipLaunchKernelGGL((evict_direct_kernel<false, 2>), grid, dim3(BT), 0, s, a);
+}
+
+struct BucketArgs {
+  EvictArgs e;
+  uint32_t B, S;       // buckets (a power of two), samples (a multiple of B)
+  uint64_t* spl_key;   // [B - 1] splitters, ascending (key, id): bucket b holds the blocks from
+  uint32_t* spl_id;    //         splitter b - 1 up to, without, splitter b
+  uint64_t* sample;    // [S] sampled keys
+  uint32_t* count;     // [B] blocks per bucket
+  uint32_t* taken;     // [B] places handed out so far
+  uint64_t* units;     // [B] size units per bucket (with sizes)
+  uint32_t* first;     // [B + 1] blocks below each bucket
+  uint64_t* below;     // [B + 1] size units below each bucket
+  uint32_t* over;      // 1: some bucket is larger than BUCKET_CAP
+  uint64_t* err;       // device error bits
+  uint64_t* key;       // [N] keys, bucket by bucket
+  uint32_t* id;        // [N] block ids, bucket by bucket
+};
+
+// Sample j's block: a pseudo-random one of the j-th of S equal stretches of
+// block ids (so sample order is id order).
+__device__ inline uint32_t sample_block(uint32_t j, uint32_t S, uint32_t N) {
+  const uint32_t lo = (uint32_t)((uint64_t)j * N / S), hi = (uint32_t)((uint64_t)(j + 1) * N / S);
+  const uint32_t h = (j * 0x9E3779B1u) ^ ((j * 0x85EBCA77u) >> 15);
+  return lo + (uint32_t)(((uint64_t)h * (hi - lo)) >> 32);
+}
+
+__device__ inline void clear_buckets(const BucketArgs& a) {
+  for (uint32_t b = threadIdx.x; b < a.B; b += BT) {
+    a.count[b] = 0;
+    a.taken[b] = 0;
+    a.units[b] = 0;
+  }
+  if (threadIdx.x == 0) {
+    *a.err = 0;
+    *a.over = 0;
+  }
+}
+
+// The sampled keys, gathered once: the splitter kernel's workgroups then read
+// them as one stretch instead of each gathering all of them line by line.
+__global__ __launch_bounds__(SAMPLE_WG) void evict_sample_kernel(BucketArgs a) {
+  const uint32_t j = blockIdx.x * SAMPLE_WG + threadIdx.x;
+  if (j >= a.S) return;
+  const uint32_t i = sample_block(j, a.S, a.e.N);
+  a.sample[j] = block_key(a.e.tier, a.e.type[i], a.e.last_access[i]);
+}
+
+// Splitters: every workgroup stages the whole sample and ranks its share;
+// every S / B-th sample is a splitter.  Also clears what the next kernels add to.
+template <int E, bool GATHERED>
+__global__ __launch_bounds__(BT) void evict_splitter_kernel(BucketArgs a) {
+  __shared__ uint64_t s_key[SAMPLES_MAX];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  if (blockIdx.x == 0) clear_buckets(a);
+  if constexpr (GATHERED) {
+    for (uint32_t j = tid; j < a.S; j += BT) s_key[j] = a.sample[j];
+  } else {
+    constexpr int U = 4;
+    for (uint32_t j0 = tid; j0 < a.S; j0 += U * BT) {
+      uint32_t ty[U];
+      uint64_t la[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t i = sample_block(min(j0 + u * BT, a.S - 1), a.S, a.e.N);
+        ty[u] = a.e.type[i];
+        la[u] = a.e.last_access[i];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j0 + u * BT < a.S) s_key[j0 + u * BT] = block_key(a.e.tier, ty[u], la[u]);
+    }
+  }
+  __syncthreads();
+  const uint32_t waves = gridDim.x * BNW, every = a.S / a.B;
+  for (uint32_t j0 = (blockIdx.x * BNW + wid) * E; j0 < a.S; j0 += E * waves) {
+    uint32_t rank[E];
+    uint64_t unused[E];
+    count_before<E, false>(s_key, nullptr, a.S / 64, j0, rank, unused);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (lane == 0 && rank[e] && rank[e] % every == 0) {
+        a.spl_key[rank[e] / every - 1] = s_key[j0 + e];
+        a.spl_id[rank[e] / every - 1] = sample_block(j0 + e, a.S, a.e.N);
+      }
+  }
+}
+
+// Bucket of (key, id): the number of splitters at or below it.
+__device__ inline uint32_t find_bucket(const uint64_t* s_key, const uint32_t* s_id, uint32_t B, uint64_t key,
+                                       uint32_t id) {
+  uint32_t pos = 0;
+  for (uint32_t step = B >> 1; step; step >>= 1) {
+    const uint64_t k = s_key[pos + step - 1];
+    if (k < key || (k == key && s_id[pos + step - 1] <= id)) pos += step;
+  }
+  return pos;
+}
+
+// Exclusive scan over the workgroup's 1024 threads; *total gets the sum.
+template <typename T>
+__device__ inline T scan_wg(T v, T* s_w, T* total) {
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const T x = wave::incl_add(v);
+  if (lane == 63) s_w[wid] = x;
+  __syncthreads();
+  const T w = lane < BNW ? s_w[lane] : T(0);
+  const T below = wave::sum(lane < wid ? w : T(0));
+  *total = wave::sum(w);
+  __syncthreads();
+  return below + x - v;
+}
+
+// Partition, IPT blocks per thread.  COUNT: blocks and size units per bucket,
+// and the validation.  Otherwise every block's key and id to its bucket's
+// stretch: workgroups reserve places in it in any order (the bucket is sorted
+// afterwards).
+template <int IPT, bool COUNT>
+__global__ __launch_bounds__(BT) void evict_partition_kernel(BucketArgs a) {
+  __shared__ uint64_t s_key[BUCKETS_MAX];
+  __shared__ uint32_t s_id[BUCKETS_MAX];
+  __shared__ uint32_t s_cnt[BUCKETS_MAX];
+  __shared__ unsigned long long s_units[COUNT ? BUCKETS_MAX : 1];
+  __shared__ uint32_t s_base[COUNT ? 1 : BUCKETS_MAX];
+  __shared__ uint32_t s_w[BNW];
+  const uint32_t tid = threadIdx.x;
+  const uint64_t i0 = (uint64_t)blockIdx.x * (BT * IPT) + tid;
+  uint32_t ty[IPT], sz[IPT];
+  uint64_t la[IPT];
+#pragma unroll
+  for (int it = 0; it < IPT; ++it) {
+    const uint32_t i = (uint32_t)min(i0 + it * BT, (uint64_t)a.e.N - 1);
+    ty[it] = a.e.type[i];
+    la[it] = a.e.last_access[i];
+    sz[it] = COUNT && a.e.size ? a.e.size[i] : 0u;
+  }
+  if (tid < a.B) {
+    s_key[tid] = tid + 1 < a.B ? a.spl_key[tid] : ~0ull;
+    s_id[tid] = tid + 1 < a.B ? a.spl_id[tid] : 0u;
+    s_cnt[tid] = 0;
+    if (COUNT) s_units[tid] = 0;
+  }
+  __syncthreads();
+  const uint32_t lane = tid & 63;
+  const uint64_t lanemask_lt = (1ull << lane) - 1ull;
+  uint32_t bkt[IPT], r[IPT], err = 0;
+#pragma unroll
+  for (int it = 0; it < IPT; ++it) {
+    const uint64_t i = i0 + it * BT;
+    const bool valid = i < a.e.N;
+    if (COUNT && valid) err |= (uint32_t)block_error(ty[it], la[it]);
+    la[it] = block_key(a.e.tier, ty[it], la[it]);
+    bkt[it] = find_bucket(s_key, s_id, a.B, la[it], (uint32_t)i);
+    r[it] = 0;
+    // A program's blocks have neighbouring ids and times, so a wave's blocks
+    // mostly share one or two buckets: those take one increment each, the
+    // rest one a lane.
+    uint64_t todo = __ballot(valid);
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+      if (todo == 0) break;
+      const int lead = __builtin_ctzll(todo);
+      const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)bkt[it], lead);
+      const bool mine = ((todo >> lane) & 1u) && bkt[it] == v;
+      const uint64_t mask = __ballot(mine);
+      uint32_t at = 0;
+      if (lane == (uint32_t)lead) at = atomicAdd(&s_cnt[v], (uint32_t)__popcll(mask));
+      if (COUNT && a.e.size) {
+        const uint64_t sum = wave::sum<uint64_t>(mine ? sz[it] : 0u);
+        if (lane == (uint32_t)lead) atomicAdd(&s_units[v], (unsigned long long)sum);
+      }
+      if (!COUNT) {
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, lead);
+        if (mine) r[it] = at + (uint32_t)__popcll(mask & lanemask_lt);
+      }
+      todo &= ~mask;
+    }
+    if ((todo >> lane) & 1u) {
+      r[it] = atomicAdd(&s_cnt[bkt[it]], 1u);
+      if (COUNT && a.e.size) atomicAdd(&s_units[bkt[it]], (unsigned long long)sz[it]);
+    }
+  }
+  if (COUNT && err) atomicOr((unsigned long long*)a.err, (unsigned long long)err);
+  __syncthreads();
+  if constexpr (COUNT) {
+    if (tid < a.B && s_cnt[tid]) {
+      atomicAdd(&a.count[tid], s_cnt[tid]);
+      if (a.e.size) atomicAdd((unsigned long long*)&a.units[tid], s_units[tid]);
+    }
+  } else {
+    uint32_t total;
+    const uint32_t count = tid < a.B ? a.count[tid] : 0u;
+    const uint32_t first = scan_wg(count, s_w, &total);
+    if (tid < a.B && s_cnt[tid]) s_base[tid] = first + atomicAdd(&a.taken[tid], s_cnt[tid]);
+    if (blockIdx.x == 0) {  // where each bucket begins, for the kernel that sorts them
+      __shared__ uint64_t s_w64[BNW];
+      uint64_t all;
+      const uint64_t below = scan_wg(tid < a.B && a.e.size ? a.units[tid] : (uint64_t)count, s_w64, &all);
+      if (tid < a.B) {
+        a.first[tid] = first;
+        a.below[tid] = below;
+        if (count > BUCKET_CAP) *a.over = 1;
+      }
+      if (tid == 0) {
+        a.first[a.B] = total;
+        a.below[a.B] = all;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+      const uint64_t i = i0 + it * BT;
+      if (i >= a.e.N) continue;
+      const uint32_t pos = s_base[bkt[it]] + r[it];
+      a.key[pos] = la[it];
+      a.id[pos] = (uint32_t)i;
+    }
+  }
+}
+
+__device__ inline bool pair_less(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
+  return ka < kb || (ka == kb && ia < ib);
+}
+
+// Order of two entries of a bucket being sorted: PACKED ones are single words
+// (key above the bucket's least, then id), the others (key, id) pairs.
+template <bool PACKED>
+__device__ inline bool entry_less(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
+  return PACKED ? ka < kb : pair_less(ka, ia, kb, ib);
+}
+
+// A wave's 64 entries ascending by lane: a bitonic network.
+template <bool PACKED>
+__device__ inline void sort_wave(uint64_t& key, uint32_t& id) {
+  const uint32_t lane = threadIdx.x & 63;
+  auto step = [&](auto D, uint32_t size) {
+    constexpr uint32_t d = decltype(D)::value;
+    const uint64_t k = wave::swap_lanes<d>(key);
+    const uint32_t i = PACKED ? 0u : wave::swap_lanes<d>(id);
+    const bool low = (lane & d) == 0, up = (lane & size) == 0;
+    if (entry_less<PACKED>(k, i, key, id) == (low == up)) {
+      key = k;
+      if (!PACKED) id = i;
+    }
+  };
+#pragma unroll
+  for (uint32_t size = 2; size <= 64; size <<= 1) {
+    if (size >= 64) step(std::integral_constant<uint32_t, 32>(), size);
+    if (size >= 32) step(std::integral_constant<uint32_t, 16>(), size);
+    if (size >= 16) step(std::integral_constant<uint32_t, 8>(), size);
+    if (size >= 8) step(std::integral_constant<uint32_t, 4>(), size);
+    if (size >= 4) step(std::integral_constant<uint32_t, 2>(), size);
+    step(std::integral_constant<uint32_t, 1>(), size);
+  }
+}
+
+// Sorts the bucket's n entries (this thread's: key[it], id[it] at it * BT + tid,
+// padded to m, a multiple of 64, with entries above every real one) into s_key
+// (and s_id unless PACKED): waves sort 64 entries each in registers, then
+// sorted lists are merged two by two, each entry finding its place by a binary
+// search in the sibling list.
+template <bool PACKED>
+__device__ inline void sort_bucket(uint64_t (&key)[BUCKET_IPT], uint32_t (&id)[BUCKET_IPT], uint32_t m,
+                                   uint64_t* s_key, uint32_t* s_id) {
+  const uint32_t tid = threadIdx.x;
+  uint32_t to[BUCKET_IPT];
+#pragma unroll
+  for (int it = 0; it < BUCKET_IPT; ++it) {
+    const uint32_t x = it * BT + tid;
+    if (x >= m) break;  // whole waves
+    sort_wave<PACKED>(key[it], id[it]);
+    s_key[x] = key[it];
+    if (!PACKED) s_id[x] = id[it];
+  }
+  __syncthreads();
+  for (uint32_t L = 64; L < m; L <<= 1) {
+#pragma unroll
+    for (int it = 0; it < BUCKET_IPT; ++it) {
+      const uint32_t x = it * BT + tid;
+      if (x >= m) break;
+      const uint32_t own = x & ~(L - 1), sib = own ^ L;
+      key[it] = s_key[x];
+      if (!PACKED) id[it] = s_id[x];
+      uint32_t lo = 0, hi = sib < m ? min(L, m - sib) : 0u;  // entries of the sibling list below this one (none equal)
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        const uint64_t k = s_key[sib + mid];
+        const bool lt = PACKED ? k < key[it] : k < key[it] || (k == key[it] && s_id[sib + mid] < id[it]);
+        if (lt) lo = mid + 1;
+        else hi = mid;
+      }
+      to[it] = min(own, sib) + (x - own) + lo;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < BUCKET_IPT; ++it) {
+      const uint32_t x = it * BT + tid;
+      if (x >= m) break;
+      s_key[to[it]] = key[it];
+      if (!PACKED) s_id[to[it]] = id[it];
+    }
+    __syncthreads();
+  }
+}
+
+// One bucket per workgroup, sorted in LDS and written out with the prefix.
+// Where the bucket's keys span less than 2^44 (all but the few buckets that
+// hold two types, in practice), key and id fit one word: one compare and two
+// registers an entry instead of three and three.  A bucket of more than
+// BUCKET_CAP blocks, which only a sample that misses the distribution leaves,
+// is ranked by counting, in which all workgroups share.
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(8))) void evict_bucket_kernel(BucketArgs a) {
+  __shared__ uint64_t s_key[BUCKET_CAP];
+  __shared__ uint32_t s_id[BUCKET_CAP];
+  __shared__ uint64_t s_w64[BNW];
+  __shared__ uint32_t s_wide;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint64_t unit = a.e.unit_bytes;
+  const uint64_t err = *a.err;
+  const uint32_t first = a.first[blockIdx.x], n = a.first[blockIdx.x + 1] - first;
+  uint64_t below = a.below[blockIdx.x];
+  const uint64_t least = blockIdx.x ? a.spl_key[blockIdx.x - 1] : 0ull;  // no key of the bucket is below it
+  if (blockIdx.x == 0 && tid == 0) finish_result(a.e, err, a.below[a.B] * unit);
+  if (err) return;
+  if (tid == 0) s_wide = 0;
+  if (*a.over)
+    for (uint32_t b = 0; b < a.B; ++b) {
+      const uint32_t first = a.first[b], n = a.first[b + 1] - first;
+      const uint64_t below = a.below[b];
+      if (n > BUCKET_CAP)
+        for (uint32_t x = blockIdx.x * BNW + wid; x < n; x += gridDim.x * BNW) {
+          const uint64_t k = a.key[first + x];
+          const uint32_t id = a.id[first + x];
+          uint32_t rank = 0;
+          uint64_t before = 0;
+          for (uint32_t j = lane; j < n; j += 64) {
+            const uint32_t ij = a.id[first + j];
+            if (pair_less(a.key[first + j], ij, k, id)) {
+              ++rank;
+              before += a.e.size ? a.e.size[ij] : 1u;
+            }
+          }
+          rank = wave::sum(rank);
+          before = wave::sum(before);
+          const uint64_t own = a.e.size ? a.e.size[id] : 1u;
+          if (lane == 0) emit(a.e, first + rank, id, (below + before + own) * unit, own * unit);
+        }
+    }
+  if (n == 0 || n > BUCKET_CAP) return;
+  const uint32_t m = (n + 63) & ~63u;
+  uint64_t key[BUCKET_IPT];
+  uint32_t id[BUCKET_IPT];
+  bool wide = false;
+#pragma unroll
+  for (int it = 0; it < BUCKET_IPT; ++it) {
+    const uint32_t x = it * BT + tid;
+    if (x >= m) break;
+    key[it] = x < n ? a.key[first + x] : ~0ull;
+    id[it] = x < n ? a.id[first + x] : ~0u;
+    wide |= x < n && ((key[it] - least) >> (64 - BUCKET_ID_BITS)) != 0;
+  }
+  __syncthreads();  // s_wide is zero
+  if (wide) s_wide = 1;
+  __syncthreads();
+  const bool packed = !s_wide;
+  if (packed) {
+#pragma unroll
+    for (int it = 0; it < BUCKET_IPT; ++it) {
+      const uint32_t x = it * BT + tid;
+      if (x >= m) break;
+      if (x < n) key[it] = ((key[it] - least) << BUCKET_ID_BITS) | id[it];
+    }
+    sort_bucket<true>(key, id, m, s_key, s_id);
+  } else {
+    sort_bucket<false>(key, id, m, s_key, s_id);
+  }
+#pragma unroll
+  for (int it = 0; it < BUCKET_IPT; ++it) {
+    if (it * BT >= n) break;  // uniform
+    const uint32_t x = it * BT + tid;
+    const uint32_t b = x >= n ? 0u : packed ? (uint32_t)s_key[x] & ((1u << BUCKET_ID_BITS) - 1) : s_id[x];
+    const uint64_t own = x >= n ? 0ull : a.e.size ? a.e.size[b] : 1ull;
+    uint64_t sum;
+    const uint64_t ex = scan_wg(own, s_w64, &sum);
+    if (x < n) emit(a.e, first + x, b, (below + ex + own) * unit, own * unit);
+    below += sum;
+  }
+}
+
+void launch_buckets(const EvictArgs& e, uint8_t* w, hipStream_t s) {
+  const uint32_t N = e.N;
+  BucketArgs a{};
+  a.e = e;
+  a.B = 64;
+  while (a.B < BUCKETS_MAX && (uint64_t)a.B * BUCKET_AVG < N) a.B *= 2;
+  a.S = std::max(a.B * SAMPLES_PER_BUCKET, SAMPLES_MIN);
+  auto take = [&w](uint64_t bytes) {
+    uint8_t* r = w;
+    w += (bytes + 255) & ~255ull;
+    return r;
+  };
+  a.key = reinterpret_cast<uint64_t*>(take(8ull * N));
+  a.id = reinterpret_cast<uint32_t*>(take(4ull * N));
+  a.spl_key = reinterpret_cast<uint64_t*>(take(8 * BUCKETS_MAX));
+  a.units = reinterpret_cast<uint64_t*>(take(8 * BUCKETS_MAX));
+  a.spl_id = reinterpret_cast<uint32_t*>(take(4 * BUCKETS_MAX));
+  a.count = reinterpret_cast<uint32_t*>(take(4 * BUCKETS_MAX));
+  a.taken = reinterpret_cast<uint32_t*>(take(4 * BUCKETS_MAX));
+  a.first = reinterpret_cast<uint32_t*>(take(4 * (BUCKETS_MAX + 1)));
+  a.below = reinterpret_cast<uint64_t*>(take(8 * (BUCKETS_MAX + 1)));
+  a.over = reinterpret_cast<uint32_t*>(take(4));
+  a.sample = reinterpret_cast<uint64_t*>(take(8 * SAMPLES_MAX));
+  a.err = reinterpret_cast<uint64_t*>(take(8));
+  if (a.S <= DIRECT_WG * BNW) {
+    hipLaunchKernelGGL((evict_splitter_kernel<1, false>), dim3(DIRECT_WG), dim3(BT), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(evict_sample_kernel, dim3((a.S + SAMPLE_WG - 1) / SAMPLE_WG), dim3(SAMPLE_WG), 0, s, a);
+    hipLaunchKernelGGL((evict_splitter_kernel<2, true>), dim3(DIRECT_WG), dim3(BT), 0, s, a);
+  }
+  if (N <= PARTITION_ONE_MAX) {
+    const dim3 grid((N + BT - 1) / BT);
+    hipLaunchKernelGGL((evict_partition_kernel<1, true>), grid, dim3(BT), 0, s, a);
+    hipLaunchKernelGGL((evict_partition_kernel<1, false>), grid, dim3(BT), 0, s, a);
+  } else {
+    const dim3 grid((N + 2 * BT - 1) / (2 * BT));
+    hipLaunchKernelGGL((evict_partition_kernel<2, true>), grid, dim3(BT), 0, s, a);
+    hipLaunchKernelGGL((evict_partition_kernel<2, false>), grid, dim3(BT), 0, s, a);
+  }
+  hipLaunchKernelGGL(evict_bucket_kernel, dim3(a.B), dim3(BT), 0, s, a);
+}
+
+void launch_radix(EvictArgs& a, uint8_t* w, hipStream_t s) {
+  const uint64_t tile = (uint64_t)ET * EIPT;
+  const uint64_t N = a.N;
+  a.ntiles = (uint32_t)((N + tile - 1) / tile);
   auto up = [](uint64_t b) { return (b + 255) & ~255ull; };
-  uint8_t* w = static_cast<uint8_t*>(workspace);
   a.keys[0] = reinterpret_cast<uint64_t*>(w);
   w += up(8ull * N);
   a.keys[1] = reinterpret_cast<uint64_t*>(w);
@@ -748,37 +1116,48 @@ hipError_t launch_evict(uint32_t N, const uint8_t* type, const uint64_t* last_ac
   w += up(4ull * 256 * a.ntiles);
   a.dtot = reinterpret_cast<uint32_t*>(w);
   w += up(4 * 256);
-  a.onesweep = a.ntiles <= ONESWEEP_TILES;
-  for (int b = 0; b < 2; ++b) {
-    a.status[b] = reinterpret_cast<uint64_t*>(w);
-    w += up(8ull * 256 * a.ntiles);
-  }
-  a.part = reinterpret_cast<uint32_t*>(w);
-  w += up(4ull * KEY_WG_MAX * 8 * 256);
-  a.gtot = reinterpret_cast<uint32_t*>(w);
-  w += up(4 * 8 * 256);
-  a.tile_ctr = reinterpret_cast<uint32_t*>(w);
-  w += up(4 * 8);
   a.tile_sum = reinterpret_cast<uint64_t*>(w);
   w += up(8ull * a.ntiles);
-  uint64_t* prefix_tmp = reinterpret_cast<uint64_t*>(w);
+  if (!a.prefix) a.prefix = reinterpret_cast<uint64_t*>(w);
   w += up(8ull * N);
   a.misc = reinterpret_cast<uint64_t*>(w);
-  a.order = order;
-  a.prefix = prefix ? prefix : prefix_tmp;
-  a.result = result;
-  const uint32_t tiles = a.ntiles ? a.ntiles : 1;
-  hipLaunchKernelGGL(evict_init_kernel, dim3(tiles < 256 ? tiles : 256), dim3(ET), 0, s, a);
-  a.key_wg = tiles < KEY_WG_MAX ? tiles : KEY_WG_MAX;
-  if (a.onesweep) hipLaunchKernelGGL(evict_keys_kernel<KEYS_PER_ROUND_SMALL>, dim3(a.key_wg), dim3(ET), 0, s, a);
-  else hipLaunchKernelGGL(evict_keys_kernel<KEYS_PER_ROUND_LARGE>, dim3(a.key_wg), dim3(ET), 0, s, a);
-  if (a.onesweep) hipLaunchKernelGGL(evict_totals_kernel, dim3(8 * TOT_SPLIT), dim3(ET), 0, s, a);
-  if (a.ntiles) {
-    if (kpt == 4) launch_tiles<4>(a, s);
-    else launch_tiles<8>(a, s);
+  hipLaunchKernelGGL(evict_init_kernel, dim3(1), dim3(1), 0, s, a);
+  hipLaunchKernelGGL(evict_keys_kernel, dim3(a.ntiles < KEY_WG_MAX ? a.ntiles : KEY_WG_MAX), dim3(ET), 0, s, a);
+  for (int shift = 0; shift < 64; shift += 8) {
+    hipLaunchKernelGGL(evict_hist_kernel, dim3(a.ntiles), dim3(ET), 0, s, a, shift);
+    hipLaunchKernelGGL(evict_dscan_kernel, dim3(256), dim3(ET), 0, s, a, shift);
+    hipLaunchKernelGGL(evict_scatter_kernel, dim3(a.ntiles), dim3(ET), 0, s, a, shift);
+  }
+  hipLaunchKernelGGL(evict_prefix_tiles_kernel, dim3(a.ntiles), dim3(ET), 0, s, a);
+  if (a.ntiles <= FIX_SCAN_TILES) {
+    hipLaunchKernelGGL(evict_prefix_fix_scan_kernel, dim3(a.ntiles), dim3(ET), 0, s, a);
   } else {
+    hipLaunchKernelGGL(evict_prefix_top_kernel, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(evict_prefix_fix_kernel, dim3(a.ntiles), dim3(ET), 0, s, a);
     hipLaunchKernelGGL(evict_result_kernel, dim3(1), dim3(1), 0, s, a);
   }
+}
+
+}  // namespace
+
+hipError_t launch_evict(uint32_t N, const uint8_t* type, const uint64_t* last_access, const uint32_t* size,
+                        uint64_t unit_bytes, uint32_t tier, uint64_t need, void* workspace, uint32_t* order,
+                        uint64_t* prefix, uint32_t* result, hipStream_t s) {
+  EvictArgs a{};
+  a.N = N;
+  a.tier = tier;
+  a.type = type;
+  a.last_access = last_access;
+  a.size = size;
+  a.unit_bytes = unit_bytes;
+  a.need = need;
+  a.order = order;
+  a.prefix = prefix;
+  a.result = result;
+  uint8_t* w = static_cast<uint8_t*>(workspace);
+  if (N <= DIRECT_MAX) launch_direct(a, s);
+  else if (N <= BUCKET_MAX) launch_buckets(a, w, s);
+  else launch_radix(a, w, s);
   return hipGetLastError();
 }
 

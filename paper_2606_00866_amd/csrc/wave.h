@@ -64,6 +64,26 @@ __device__ inline T all_or(T v) { return lane63(incl(v, Or())); }
 template <typename T>
 __device__ inline T all_and(T v) { return ~all_or<T>(~v); }
 
+// v of lane ^ D: on the DPP paths within a row of 16 lanes (quad permutations,
+// for 4 the mirror of eight lanes then of four, for 8 a rotation), through the
+// LDS crossbar across rows.
+template <uint32_t D>
+__device__ inline uint32_t swap_lanes(uint32_t v) {
+  constexpr int QUAD_1032 = 0xB1, QUAD_2301 = 0x4E, QUAD_3210 = 0x1B, ROW_ROR8 = 0x128, ROW_HALF_MIRROR = 0x141;
+  const int x = (int)v;
+  if constexpr (D == 1) return (uint32_t)__builtin_amdgcn_update_dpp(x, x, QUAD_1032, 0xF, 0xF, true);
+  else if constexpr (D == 2) return (uint32_t)__builtin_amdgcn_update_dpp(x, x, QUAD_2301, 0xF, 0xF, true);
+  else if constexpr (D == 4) {
+    const int y = __builtin_amdgcn_update_dpp(x, x, ROW_HALF_MIRROR, 0xF, 0xF, true);  // lane ^ 7
+    return (uint32_t)__builtin_amdgcn_update_dpp(y, y, QUAD_3210, 0xF, 0xF, true);     // ^ 3
+  } else if constexpr (D == 8) return (uint32_t)__builtin_amdgcn_update_dpp(x, x, ROW_ROR8, 0xF, 0xF, true);
+  else return (uint32_t)__shfl_xor((int)v, (int)D, 64);
+}
+template <uint32_t D>
+__device__ inline uint64_t swap_lanes(uint64_t v) {
+  return ((uint64_t)swap_lanes<D>((uint32_t)(v >> 32)) << 32) | swap_lanes<D>((uint32_t)v);
+}
+
 // The lanes whose low BITS-bit digit differs from this lane's: one ballot per
 // bit, each lane's bit sign-extended to a whole mask serving both as the
 // ballot's input and as the XOR that turns the ballot into "bit differs".
