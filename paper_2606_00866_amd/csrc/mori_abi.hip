@@ -2,7 +2,7 @@
 // pinned plan mirror, staging), stream/event ordering of the three calls, and
 // the two copy modes of the swaps.
 //
-//   plan       rank kernel (and the page state) -> page kernels, which also
+//   plan       rank kernel (and the page owners) -> page kernels, which also
 //              store the plan into its pinned host mirror -> plan event.
 //   swap-out   direct: translate addresses -> gather kernel storing straight
 //              into host-mapped memory; copy engine: per chunk, gather kernel
@@ -83,7 +83,11 @@ struct mori_ctx {
   uint8_t* blob_host_dev = nullptr;  // the mirror as the device addresses it
   uint8_t* scratch = nullptr;    // device-only arrays
   uint32_t* base = nullptr;
-  uint32_t* pstate = nullptr;
+  uint64_t* owner = nullptr;
+  uint8_t* pcode = nullptr;
+  uint32_t* page_err = nullptr;
+  uint32_t* slot_base = nullptr;
+  uint32_t* slot_prog = nullptr;
   uint32_t* out_src = nullptr;
   uint32_t* in_dst = nullptr;
   uint32_t* ord = nullptr;
@@ -105,6 +109,7 @@ struct mori_ctx {
   hipEvent_t ev_start[2] = {nullptr, nullptr};
   std::vector<DevRange> ranges;
   hipEvent_t ev_plan = nullptr, ev_out = nullptr, ev_in = nullptr, ev_addr[2] = {nullptr, nullptr};
+  bool owner_stale = false;
   bool have_plan = false, out_enqueued = false, in_enqueued = false;
   bool out_recorded = false, in_recorded = false, addr_pending[2] = {false, false};
   uint32_t P = 0;
@@ -240,14 +245,19 @@ extern "C" int mori_create(const mori_pool* pool, uint32_t max_programs, uint64_
     o += (bytes + 255) & ~size_t(255);
     return r;
   };
-  const size_t o_base = take(4 * pm), o_pstate = take(4 * NB), o_out_src = take(4 * NB), o_in_dst = take(4 * NB);
+  const size_t o_base = take(4 * pm), o_owner = take(8 * NB), o_pcode = take(NB), o_page_err = take(4);
+  const size_t o_slot_base = take(4 * pm), o_slot_prog = take(4 * pm), o_out_src = take(4 * NB), o_in_dst = take(4 * NB);
   const size_t o_ord = take(4 * pm), o_out_ord = take(4 * NB), o_in_ord = take(4 * NB);
   const size_t o_tc = take(16ull * c->ntiles), o_tb = take(16ull * c->ntiles);
   const size_t o_ad0 = take(8 * pm), o_ad1 = take(8 * pm);
   const size_t o_err = take(8), o_rng = take(sizeof(DevRange) * MORI_MAX_RANGES), o_sr = take(2 * sizeof(SwapRange));
   if ((e = hipMalloc(&c->scratch, o)) != hipSuccess) return fail(e);
   c->base = reinterpret_cast<uint32_t*>(c->scratch + o_base);
-  c->pstate = reinterpret_cast<uint32_t*>(c->scratch + o_pstate);
+  c->owner = reinterpret_cast<uint64_t*>(c->scratch + o_owner);
+  c->pcode = c->scratch + o_pcode;
+  c->page_err = reinterpret_cast<uint32_t*>(c->scratch + o_page_err);
+  c->slot_base = reinterpret_cast<uint32_t*>(c->scratch + o_slot_base);
+  c->slot_prog = reinterpret_cast<uint32_t*>(c->scratch + o_slot_prog);
   c->out_src = reinterpret_cast<uint32_t*>(c->scratch + o_out_src);
   c->in_dst = reinterpret_cast<uint32_t*>(c->scratch + o_in_dst);
   c->ord = reinterpret_cast<uint32_t*>(c->scratch + o_ord);
@@ -391,7 +401,11 @@ extern "C" int mori_rank_partition(mori_ctx* ctx, const mori_programs* pr, const
   a.out_pg_base = ctx->dev<uint32_t>(ctx->L.out_base);
   a.in_pg_base = ctx->dev<uint32_t>(ctx->L.in_base);
   a.base = ctx->base;
-  a.pstate = ctx->pstate;
+  a.owner = ctx->owner;
+  a.pcode = ctx->pcode;
+  a.page_err = ctx->page_err;
+  a.slot_base = ctx->slot_base;
+  a.slot_prog = ctx->slot_prog;
   a.out_src = ctx->out_src;
   a.in_dst = ctx->in_dst;
   a.ord = ctx->ord;
@@ -401,8 +415,13 @@ extern "C" int mori_rank_partition(mori_ctx* ctx, const mori_programs* pr, const
   a.tile_base = ctx->tile_base;
   a.swap_err = ctx->swap_err;
   a.host_delta = reinterpret_cast<int64_t>(ctx->blob_host_dev) - reinterpret_cast<int64_t>(ctx->blob_dev);
+  // the kernels leave the page owners and their error word cleared for the next
+  // plan; a plan whose launches failed half way may not have
+  if (ctx->owner_stale) HIP_TRY(ctx, launch_clear_owner(a, s));
+  ctx->owner_stale = true;
   HIP_TRY(ctx, launch_rank(a, s));
   HIP_TRY(ctx, launch_pages(a, s));
+  ctx->owner_stale = false;
   HIP_TRY(ctx, hipEventRecord(ctx->ev_plan, s));
   ctx->have_plan = true;
   ctx->out_enqueued = ctx->in_enqueued = false;

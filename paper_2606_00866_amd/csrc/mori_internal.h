@@ -8,16 +8,15 @@
 
 namespace mori {
 
-// Page-state bits of the page-allocation pass.
-constexpr uint32_t PS_FREE = 1u;   // marked free in the caller's free map before the step
-constexpr uint32_t PS_OWNED = 2u;  // owned by a GPU-resident program
-constexpr uint32_t PS_REL = 4u;    // owned by a program leaving the GPU this step
-constexpr uint32_t PS_LATER = 8u;  // ... and free only after the swap-out stream has passed: the
-                                   // swap-out reads it, or its dropped program may still be running
+// What the step does with a page.
+constexpr uint32_t PC_KEPT = 0u;   // owned by a program that stays on the GPU
+constexpr uint32_t PC_FREE = 1u;   // marked free in the caller's free map before the step
+constexpr uint32_t PC_REL = 2u;    // owned by a program leaving the GPU, free at once
+constexpr uint32_t PC_LATER = 3u;  // ... free only after the swap-out stream has passed: the swap-out
+                                   // reads it, or its dropped program may still be running
 
 constexpr int PAGE_TILE = 512;     // pages per workgroup in the page-allocation kernels (2 per thread;
                                    // measured: 0.5-1 us faster per plan than 1024, 2048 slower)
-constexpr int PAGE_WG = 256;       // threads per page-allocation workgroup (16 pages each)
 
 // Plan summary as kept on the device (the head of the plan blob, mirrored on the host).
 struct DevSummary {
@@ -64,7 +63,11 @@ struct PlanArgs {
   uint32_t* in_pg_base;   // [n_in + 1] first slot of each in program
   // context scratch: device only
   uint32_t* base;         // per program: out-page base (OUT) or slot base (IN, ADMIT_GPU)
-  uint32_t* pstate;       // [NB]
+  uint64_t* owner;        // [NB] program << 32 | (table entry + 1) of each owned page, 0 between plans
+  uint8_t* pcode;         // [NB] PC_* of each page
+  uint32_t* page_err;     // ownership errors, 0 between plans
+  uint32_t* slot_base;    // [n_in + n_admit_gpu] first slot of each program entering the GPU, in slot order
+  uint32_t* slot_prog;    // [n_in + n_admit_gpu] that program
   uint32_t* out_src;      // [pages_out] old page of each out page index
   uint32_t* in_dst;       // [need] page of each slot
   uint32_t* ord;          // per program: its index in the swap-out or swap-in list (OUT, IN)
@@ -145,6 +148,7 @@ constexpr uint64_t evict_workspace_bytes(uint32_t N) {
 
 // launchers (return the launch error)
 hipError_t launch_rank(const PlanArgs& a, hipStream_t s);
+hipError_t launch_clear_owner(const PlanArgs& a, hipStream_t s);
 hipError_t launch_pages(const PlanArgs& a, hipStream_t s);
 hipError_t launch_translate(const TranslateArgs& a, hipStream_t s);
 hipError_t launch_swap_out(const SwapArgs& a, uint32_t grid, hipStream_t s);

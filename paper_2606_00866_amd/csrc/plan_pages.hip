@@ -1,18 +1,14 @@
 // Page side of one rebalance (sticky placement of Sec. 4.3 over the paged KV
-// pool of Sec. 2.1), after the rank / boundary kernel (whose other workgroups
-// set the page state from the caller's free map):
+// pool of Sec. 2.1), after the rank / boundary kernel, whose other workgroups
+// found the owner of every page and the ownership errors meanwhile:
 //
-//   claim    walk every block-table entry: validate ownership (no page owned
-//            twice, none both owned and free, none out of range, no page held
-//            by a CPU/Waiting program), mark pages of programs leaving the
-//            GPU as released, record the old page of every swap-out block;
 //   count    per 512-page tile: pages free before the step, released pages
 //            free at once (programs dropped to Waiting that are idle) and
 //            released pages free only later (programs swapped out, and
 //            programs dropped while they may still run an inference step:
 //            Sec. 4.3.1 demotes a Reasoning victim lazily, so its step goes
 //            on reading and appending to its pages); a page that is neither
-//            free nor owned is a leak;
+//            free nor owned is a leak; the old page of every swap-out block;
 //   scan     exclusive prefix over tiles, totals, capacity; the summary is
 //            final here and is stored into the host mirror.  Up to
 //            SCAN_IN_ASSIGN tiles every assign workgroup does this itself
@@ -23,11 +19,18 @@
 //            pages nothing uses come before pages still in use, so the
 //            swap-in waits for the swap-out stream only for slots past the
 //            first two groups; the free map after the step is what is left
-//            of that sequence;
-//   commit   rewrite the block tables (released -> no page, incoming -> their
-//            slots' pages) and the tier vector.
+//            of that sequence.  A page knows its table entry (the owner's, or
+//            its slot's), so the block tables are rewritten here as well
+//            (released -> no page, incoming -> their slots' pages), and the
+//            tier vector.
 //
-// Validation happens in claim/count/scan; assign and commit write caller
+// All of it is a chain of dependent launches, bound by latency: finding the
+// owners beside the ranking and rewriting the tables from the pages leaves two
+// launches of 3-9 us after the rank kernel where there were four (a pair of
+// plans: 8 programs 56.5 -> 52 us, 256 programs 76 -> 70, 4096 programs with
+// 400 000 pages 129 -> 121).
+//
+// Validation happens beside the ranking and in count/scan; assign writes caller
 // memory only when the plan's error word is still zero, so a rejected plan
 // leaves the caller's state untouched.  All loops are grid-stride over sizes
 // the host knows (tbl_len, num_blocks), bounded by device values read once.
@@ -40,72 +43,59 @@ namespace {
 constexpr int WG = 256;
 constexpr uint32_t SCAN_IN_ASSIGN = 1024;  // tiles (2^19 pages): each assign workgroup reads 16 B per tile
 
-// Largest p in [0, P) with off[p] <= e (so off[p] <= e < off[p+1] when e < off[P]).
-__device__ inline uint32_t find_program(const uint32_t* off, uint32_t P, uint32_t e) {
-  uint32_t lo = 0, hi = P;  // invariant: off[lo] <= e, answer in [lo, hi)
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (off[mid] <= e) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
-__global__ __launch_bounds__(WG) void pages_claim_kernel(PlanArgs a) {
-  if (a.sum->error) return;
-  const uint32_t used = a.tbl_off[a.P];
-  uint32_t err = 0;
-  for (uint64_t e64 = (uint64_t)blockIdx.x * WG + threadIdx.x; e64 < used; e64 += (uint64_t)gridDim.x * WG) {
-    const uint32_t e = (uint32_t)e64;  // 64-bit stride: no wrap near 2^32 entries
-    const uint32_t p = find_program(a.tbl_off, a.P, e);
-    const uint32_t pg = a.tbl[e];
-    if (a.tier_old[p] != MORI_TIER_GPU) {
-      if (pg != MORI_NO_PAGE) err |= MORI_DEV_NONRES_PAGE;
-      continue;
-    }
-    if (pg >= a.NB) {
-      err |= MORI_DEV_PAGE_RANGE;
-      continue;
-    }
-    const uint8_t c = a.cat[p];
-    // a program dropped while it may still run (with statuses: anything but
-    // Acting) frees its pages only after its step, which the caller orders
-    // before the swap-out on the swap-out stream
-    const bool running = c == MORI_CAT_DROP_GPU && (a.flags & (MORI_F_STATUS_KEY | MORI_F_INCREMENTAL)) &&
-                         a.status[p] != MORI_ST_ACTING;
-    const uint32_t leaves =
-        c == MORI_CAT_OUT || running ? (PS_REL | PS_LATER) : c == MORI_CAT_DROP_GPU ? PS_REL : 0u;
-    const uint32_t old = atomicOr(&a.pstate[pg], PS_OWNED | leaves);
-    if (old & (PS_FREE | PS_OWNED)) err |= MORI_DEV_PAGE_DUP;
-    if (c == MORI_CAT_OUT) {
-      const uint32_t k = a.base[p] + (e - a.tbl_off[p]);
-      if (k < a.NB) {  // more owned blocks than pages implies a duplicate
-        a.out_src[k] = pg;
-        a.out_ord[k] = a.ord[p];
-      } else {
-        err |= MORI_DEV_PAGE_DUP;
-      }
-    }
-  }
-  if (err) atomicOr(&a.sum->error, err);
-}
-
 __global__ __launch_bounds__(WG) void pages_count_kernel(PlanArgs a) {
   __shared__ uint32_t s_free, s_drop, s_copy, s_err;
-  if (a.sum->error) return;
+  const uint32_t rank_err = a.sum->error, page_err = *a.page_err;
+  if (rank_err) return;
+  if (page_err) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.sum->error = page_err;
+    return;
+  }
   if (threadIdx.x == 0) s_free = s_drop = s_copy = s_err = 0;
   __syncthreads();
-  const uint32_t per = PAGE_TILE / WG;
+  constexpr uint32_t per = PAGE_TILE / WG;
   const uint64_t start = (uint64_t)blockIdx.x * PAGE_TILE + (uint64_t)threadIdx.x * per;
   uint32_t nf = 0, nd = 0, nc = 0, err = 0;
+  uint64_t own[per];
+  uint8_t fre[per];
+#pragma unroll
+  for (uint32_t j = 0; j < per; ++j) {
+    const uint64_t pg = min(start + j, (uint64_t)a.NB - 1);
+    own[j] = a.owner[pg];
+    fre[j] = a.free_map[pg];
+  }
+#pragma unroll
   for (uint32_t j = 0; j < per; ++j) {
     const uint64_t pg = start + j;
     if (pg >= a.NB) break;
-    const uint32_t st = a.pstate[pg];
-    if (st == PS_FREE) ++nf;
-    else if (st & PS_LATER) ++nc;
-    else if (st & PS_REL) ++nd;
-    else if (st == 0) err |= MORI_DEV_PAGE_LEAK;
+    uint32_t code = PC_KEPT;
+    if (own[j] == 0) {
+      if (fre[j]) code = PC_FREE;
+      else err |= MORI_DEV_PAGE_LEAK;
+    } else {
+      const uint32_t p = (uint32_t)(own[j] >> 32), e = (uint32_t)own[j] - 1u;
+      const uint8_t c = a.cat[p];
+      if (c == MORI_CAT_OUT) {
+        code = PC_LATER;
+        const uint32_t k = a.base[p] + (e - a.tbl_off[p]);
+        if (k < a.NB) {  // more owned blocks than pages implies a duplicate
+          a.out_src[k] = (uint32_t)pg;
+          a.out_ord[k] = a.ord[p];
+        } else {
+          err |= MORI_DEV_PAGE_DUP;
+        }
+      } else if (c == MORI_CAT_DROP_GPU) {
+        // a program dropped while it may still run (with statuses: anything but
+        // Acting) frees its pages only after its step, which the caller orders
+        // before the swap-out on the swap-out stream
+        const bool running = (a.flags & (MORI_F_STATUS_KEY | MORI_F_INCREMENTAL)) && a.status[p] != MORI_ST_ACTING;
+        code = running ? PC_LATER : PC_REL;
+      }
+    }
+    a.pcode[pg] = (uint8_t)code;
+    nf += code == PC_FREE;
+    nd += code == PC_REL;
+    nc += code == PC_LATER;
   }
   const uint32_t wf = wave::sum(nf), wd = wave::sum(nd), wc = wave::sum(nc);  // one LDS atomic per wavefront
   if ((threadIdx.x & 63) == 0) {
@@ -181,6 +171,21 @@ __global__ __launch_bounds__(1024) void pages_scan_kernel(PlanArgs a) {
   if (threadIdx.x == 0) finish_summary(a, carry[0] & 0xFFFFFFFFull, carry[0] >> 32, carry[1]);
 }
 
+// Table entry of a slot, and with a slot of a swapped-in program its list
+// index for the swap.  Programs entering the GPU hold consecutive slots, listed
+// in slot order: the largest j with slot_base[j] <= slot (programs without
+// blocks share the base of the next one, which is listed after them).
+__device__ inline uint32_t slot_entry(const PlanArgs& a, uint32_t n_in, uint32_t n, uint32_t slot) {
+  uint32_t lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (a.slot_base[mid] <= slot) lo = mid;
+    else hi = mid;
+  }
+  if (lo < n_in) a.in_ord[slot] = lo;
+  return a.tbl_off[a.slot_prog[lo]] + (slot - a.slot_base[lo]);
+}
+
 // SCAN: the tile scan is done here (every workgroup scans the counts of the
 // tiles before its own and totals all of them; workgroup 0 finishes the
 // summary), else it comes from pages_scan_kernel.
@@ -188,11 +193,24 @@ template <bool SCAN>
 __global__ __launch_bounds__(WG) void pages_assign_kernel(PlanArgs a) {
   __shared__ uint64_t s_wave[WG / 64 + 1];
   __shared__ uint64_t s_red[WG / 64][4];
+  constexpr uint32_t per = PAGE_TILE / WG;
+  const uint64_t start = (uint64_t)blockIdx.x * PAGE_TILE + (uint64_t)threadIdx.x * per;
+  uint64_t own[per];
+  uint32_t code[per];
+#pragma unroll
+  for (uint32_t j = 0; j < per; ++j) {  // the owners are left cleared, also by a rejected plan
+    const uint64_t pg = min(start + j, (uint64_t)a.NB - 1);
+    own[j] = a.owner[pg];
+    code[j] = start + j < a.NB ? a.pcode[pg] : PC_KEPT;
+    if (start + j < a.NB) a.owner[pg] = 0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *a.page_err = 0;
   if (a.sum->error) {
     if (SCAN && blockIdx.x == 0 && threadIdx.x == 0) *host_mirror(a, a.sum) = *a.sum;
     return;
   }
   const uint64_t need = a.sum->need;
+  const uint32_t n_in = a.sum->n_in, n_slot_progs = n_in + a.sum->n_admit_gpu;
   uint64_t tb, tbc, nf_all, nd_all;
   if constexpr (SCAN) {
     uint64_t v[4] = {0, 0, 0, 0};  // prefix (free | dropped << 32), prefix free-later, and the totals
@@ -226,17 +244,12 @@ __global__ __launch_bounds__(WG) void pages_assign_kernel(PlanArgs a) {
     nf_all = a.sum->pages_free_before;
     nd_all = a.sum->pages_dropped;
   }
-  const uint32_t per = PAGE_TILE / WG;
-  const uint64_t start = (uint64_t)blockIdx.x * PAGE_TILE + (uint64_t)threadIdx.x * per;
-  uint32_t st[PAGE_TILE / WG];
   uint32_t nf = 0, nd = 0, nc = 0;
 #pragma unroll
   for (uint32_t j = 0; j < per; ++j) {
-    const uint64_t pg = start + j;
-    st[j] = pg < a.NB ? a.pstate[pg] : PS_OWNED;
-    if (st[j] == PS_FREE) ++nf;
-    else if (st[j] & PS_LATER) ++nc;
-    else if (st[j] & PS_REL) ++nd;
+    nf += code[j] == PC_FREE;
+    nd += code[j] == PC_REL;
+    nc += code[j] == PC_LATER;
   }
   uint64_t tot;
   const uint64_t ex = wg_scan_excl<WG>((uint64_t)nf | ((uint64_t)nd << 32), s_wave, &tot);
@@ -246,36 +259,25 @@ __global__ __launch_bounds__(WG) void pages_assign_kernel(PlanArgs a) {
   uint64_t ci = tbc + exc;
 #pragma unroll
   for (uint32_t j = 0; j < per; ++j) {
+    if (code[j] == PC_KEPT) continue;
     const uint64_t pg = start + j;
-    uint64_t slot;
-    if (st[j] == PS_FREE) slot = fi++;
-    else if (st[j] & PS_LATER) slot = nf_all + nd_all + ci++;
-    else if (st[j] & PS_REL) slot = nf_all + di++;
-    else continue;
+    const uint64_t slot = code[j] == PC_FREE ? fi++ : code[j] == PC_REL ? nf_all + di++ : nf_all + nd_all + ci++;
+    if (code[j] != PC_FREE) a.tbl[(uint32_t)own[j] - 1u] = MORI_NO_PAGE;
     if (slot < need) {
       a.in_dst[slot] = (uint32_t)pg;
+      a.tbl[slot_entry(a, n_in, n_slot_progs, (uint32_t)slot)] = (uint32_t)pg;
       a.free_map[pg] = 0;
     } else {
       a.free_map[pg] = 1;
     }
   }
+  for (uint32_t p = blockIdx.x * WG + threadIdx.x; p < a.P; p += gridDim.x * WG) a.tier[p] = a.tier_new[p];
 }
 
-__global__ __launch_bounds__(WG) void commit_kernel(PlanArgs a) {
-  if (a.sum->error) return;
-  const uint32_t used = a.tbl_off[a.P];
-  for (uint64_t e64 = (uint64_t)blockIdx.x * WG + threadIdx.x; e64 < used; e64 += (uint64_t)gridDim.x * WG) {
-    const uint32_t e = (uint32_t)e64;  // 64-bit stride: no wrap near 2^32 entries
-    const uint32_t p = find_program(a.tbl_off, a.P, e);
-    const uint8_t c = a.cat[p];
-    if (c == MORI_CAT_OUT || c == MORI_CAT_DROP_GPU) a.tbl[e] = MORI_NO_PAGE;
-    else if (c == MORI_CAT_IN || c == MORI_CAT_ADMIT_GPU) {
-      const uint32_t slot = a.base[p] + (e - a.tbl_off[p]);
-      a.tbl[e] = a.in_dst[slot];
-      if (c == MORI_CAT_IN) a.in_ord[slot] = a.ord[p];
-    }
-  }
-  for (uint32_t p = blockIdx.x * WG + threadIdx.x; p < a.P; p += gridDim.x * WG) a.tier[p] = a.tier_new[p];
+__global__ __launch_bounds__(WG) void clear_owner_kernel(PlanArgs a) {
+  for (uint64_t pg = (uint64_t)blockIdx.x * WG + threadIdx.x; pg < a.NB; pg += (uint64_t)gridDim.x * WG)
+    a.owner[pg] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *a.page_err = 0;
 }
 
 // Resolves every moving program's caller address through the registered
@@ -324,17 +326,9 @@ __global__ __launch_bounds__(WG) void translate_kernel(TranslateArgs t) {
   if (err) atomicOr(&t.swap_err[t.dir_in], err);
 }
 
-inline uint32_t grid_for(uint64_t n, uint32_t cap) {
-  uint64_t g = (n + WG - 1) / WG;
-  if (g < 1) g = 1;
-  return (uint32_t)(g < cap ? g : cap);
-}
-
 }  // namespace
 
 hipError_t launch_pages(const PlanArgs& a, hipStream_t s) {
-  const uint32_t ge = grid_for(a.tbl_len > a.P ? a.tbl_len : a.P, 2048);
-  hipLaunchKernelGGL(pages_claim_kernel, dim3(ge), dim3(WG), 0, s, a);
   hipLaunchKernelGGL(pages_count_kernel, dim3(a.ntiles), dim3(WG), 0, s, a);  // ntiles >= 1: the pool has a page
   if (a.ntiles <= SCAN_IN_ASSIGN) {
     hipLaunchKernelGGL(pages_assign_kernel<true>, dim3(a.ntiles), dim3(WG), 0, s, a);
@@ -342,7 +336,11 @@ hipError_t launch_pages(const PlanArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(pages_scan_kernel, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(pages_assign_kernel<false>, dim3(a.ntiles), dim3(WG), 0, s, a);
   }
-  hipLaunchKernelGGL(commit_kernel, dim3(ge), dim3(WG), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_clear_owner(const PlanArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(clear_owner_kernel, dim3(a.ntiles < 1024 ? a.ntiles : 1024), dim3(WG), 0, s, a);
   return hipGetLastError();
 }
 

@@ -90,6 +90,44 @@ __device__ inline void add_to(unsigned long long* dst, uint64_t v) {
   if ((threadIdx.x & 63) == 0 && t) atomicAdd(dst, (unsigned long long)t);
 }
 
+// Largest p in [0, P) with off[p] <= e (so off[p] <= e < off[p+1] when e < off[P]).
+__device__ inline uint32_t find_program(const uint32_t* off, uint32_t P, uint32_t e) {
+  uint32_t lo = 0, hi = P;  // invariant: off[lo] <= e, answer in [lo, hi)
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (off[mid] <= e) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// Owner of every page, from the block tables alone (the placement is not known
+// yet), and the ownership errors: a page owned twice, owned and free or out of
+// range, a page held by a CPU/Waiting program.  Workgroup b of nb.  The program
+// data is validated by the ranking workgroup at the same time, so nothing here
+// relies on it: entries are bounded by the table, programs by P.
+__device__ void claim_pages(const PlanArgs& a, uint32_t b, uint32_t nb) {
+  if (a.P == 0) return;
+  const uint32_t used = min(a.tbl_off[a.P], a.tbl_len);
+  uint32_t err = 0;
+  for (uint64_t e64 = (uint64_t)b * blockDim.x + threadIdx.x; e64 < used; e64 += (uint64_t)nb * blockDim.x) {
+    const uint32_t e = (uint32_t)e64;  // 64-bit stride: no wrap near 2^32 entries
+    const uint32_t pg = a.tbl[e];
+    const uint32_t p = find_program(a.tbl_off, a.P, e);
+    if (a.tier[p] != MORI_TIER_GPU) {
+      if (pg != MORI_NO_PAGE) err |= MORI_DEV_NONRES_PAGE;
+      continue;
+    }
+    if (pg >= a.NB) {
+      err |= MORI_DEV_PAGE_RANGE;
+      continue;
+    }
+    const unsigned long long mine = ((unsigned long long)p << 32) | (e + 1u);
+    if (atomicExch((unsigned long long*)&a.owner[pg], mine) != 0 || a.free_map[pg]) err |= MORI_DEV_PAGE_DUP;
+  }
+  if (err) atomicOr(a.page_err, err);
+}
+
 // Transition category.  Leaving the GPU for a tier that keeps the KV (CPU,
 // SSD) is a swap-out, the reverse a swap-in.
 __device__ inline uint8_t category(uint8_t from, uint8_t to) {
@@ -120,21 +158,17 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   __shared__ uint8_t s_tier[RT * IPT];
   __shared__ uint32_t s_nblk[RT * IPT];  // blocks of program x
   __shared__ uint8_t s_told[RT * IPT];   // old tier of program x
-  __shared__ uint64_t s_tot[(IPT * NW + 1) * 2];
+  __shared__ uint64_t s_tot[(IPT * NW + 1) * 3];
   __shared__ uint32_t s_w32[NW + 1];
   __shared__ unsigned long long s_or, s_and;
   __shared__ uint32_t s_err, s_m_gpu, s_m_cpu, s_m_ssd;
   __shared__ uint32_t s_grp[5], s_cpu_reasoning, s_k_gpu, s_k_cpu;
-  __shared__ uint32_t s_n_drop_gpu, s_n_drop_cpu, s_n_admit_gpu, s_n_admit_cpu;
+  __shared__ uint32_t s_n_drop_gpu, s_n_drop_cpu, s_n_admit_cpu;
   __shared__ unsigned long long s_gpu_after, s_cpu_after, s_ssd_after, s_gpu_part, s_upper_part;
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  if (blockIdx.x > 0) {
-    // the other workgroups set up the page state for the page kernels (it
-    // depends on the caller's free map only)
-    const uint64_t stride = (uint64_t)(gridDim.x - 1) * RT;
-    for (uint64_t pg = (uint64_t)(blockIdx.x - 1) * RT + tid; pg < a.NB; pg += stride)
-      a.pstate[pg] = a.free_map[pg] ? PS_FREE : 0u;
+  if (blockIdx.x > 0) {  // the other workgroups find the pages' owners meanwhile
+    claim_pages(a, blockIdx.x - 1, gridDim.x - 1);
     return;
   }
   const uint32_t P = a.P;
@@ -148,7 +182,7 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     s_m_gpu = s_m_cpu = s_m_ssd = 0;
     for (int g = 0; g < 5; ++g) s_grp[g] = 0;
     s_cpu_reasoning = s_k_gpu = s_k_cpu = 0;
-    s_n_drop_gpu = s_n_drop_cpu = s_n_admit_gpu = s_n_admit_cpu = 0;
+    s_n_drop_gpu = s_n_drop_cpu = s_n_admit_cpu = 0;
     s_gpu_after = s_cpu_after = s_ssd_after = 0;
     s_gpu_part = s_upper_part = 0;
   }
@@ -611,17 +645,17 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   __syncthreads();
 
   // ---- 4. sticky diff: categories, lists in rank order, bases -----------
-  // packed scans: A = pages_out | pages_in << 32, B = pages_admit | n_out << 32 | n_in << 48
+  // packed scans: A = pages_out | pages_in << 32, B = pages_admit | n_out << 32 | n_in << 48, and n_admit_gpu
   // Global stores wait until after the last barrier: a barrier waits for the
   // stores still in flight, so stores issued earlier would stall every one.
-  uint64_t vab[IPT][2], exab[IPT][2], totab[2];
+  uint64_t vab[IPT][3], exab[IPT][3], totab[3];
   uint8_t catv[IPT], tnewv[IPT];
-  uint32_t n_dg = 0, n_dc = 0, n_ag = 0, n_ac = 0;
+  uint32_t n_dg = 0, n_dc = 0, n_ac = 0;
   uint64_t gpu_after = 0, cpu_after = 0, ssd_after = 0;
 #pragma unroll
   for (int it = 0; it < IPT; ++it) {
     const uint32_t r = it * RT + tid;
-    uint64_t va = 0, vb = 0;
+    uint64_t va = 0, vb = 0, vc = 0;
     catv[it] = MORI_CAT_KEPT;
     if (r < P) {
       const uint32_t p = id[it];
@@ -631,7 +665,7 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
       tnewv[it] = tnew;
       if (c == MORI_CAT_OUT) va = nb[it], vb = 1ull << 32;
       if (c == MORI_CAT_IN) va = (uint64_t)nb[it] << 32, vb = 1ull << 48;
-      if (c == MORI_CAT_ADMIT_GPU) vb = nb[it], ++n_ag;
+      if (c == MORI_CAT_ADMIT_GPU) vb = nb[it], vc = 1;
       if (c == MORI_CAT_DROP_GPU) ++n_dg;
       if (c == MORI_CAT_DROP_CPU) ++n_dc;
       if (c == MORI_CAT_ADMIT_CPU) ++n_ac;
@@ -641,12 +675,14 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     }
     vab[it][0] = va;
     vab[it][1] = vb;
+    vab[it][2] = vc;
   }
-  scan_slices<NW, IPT, 2>(vab, exab, s_tot, totab);
+  scan_slices<NW, IPT, 3>(vab, exab, s_tot, totab);
   const uint64_t carryA = totab[0], carryB = totab[1];
   const uint32_t pages_out = (uint32_t)(carryA & 0xFFFFFFFFu), pages_in = (uint32_t)(carryA >> 32);
   const uint32_t pages_admit = (uint32_t)(carryB & 0xFFFFFFFFu);
   const uint32_t n_out = (uint32_t)((carryB >> 32) & 0xFFFFu), n_in = (uint32_t)(carryB >> 48);
+  const uint32_t n_admit = (uint32_t)totab[2];
   // program-indexed staging, so the per-program stores below are coalesced:
   // the new tier and the page base by program id (every read of the
   // rank-indexed s_tier and s_nblk came before the scan's first barrier)
@@ -663,7 +699,6 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   }
   add_to(&s_n_drop_gpu, n_dg);
   add_to(&s_n_drop_cpu, n_dc);
-  add_to(&s_n_admit_gpu, n_ag);
   add_to(&s_n_admit_cpu, n_ac);
   add_to(&s_gpu_after, gpu_after);
   add_to(&s_cpu_after, cpu_after);
@@ -696,8 +731,15 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
       a.ord[p] = idx_in;
       a.in_prog[idx_in] = p;
       a.in_pg_base[idx_in] = pg;
+      a.slot_base[idx_in] = pg;
+      a.slot_prog[idx_in] = p;
       *host_mirror(a, a.in_prog + idx_in) = p;
       *host_mirror(a, a.in_pg_base + idx_in) = pg;
+    }
+    if (catv[it] == MORI_CAT_ADMIT_GPU) {  // then the programs admitted from Waiting: priority (2)
+      const uint32_t idx = n_in + (uint32_t)exab[it][2];
+      a.slot_base[idx] = pages_in + (uint32_t)(exB & 0xFFFFFFFFu);
+      a.slot_prog[idx] = p;
     }
   }
   // by program id: tiers, categories and the page bases (swap-outs from their
@@ -730,7 +772,7 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     z.n_in = n_in;
     z.n_drop_gpu = s_n_drop_gpu;
     z.n_drop_cpu = s_n_drop_cpu;
-    z.n_admit_gpu = s_n_admit_gpu;
+    z.n_admit_gpu = n_admit;
     z.n_admit_cpu = s_n_admit_cpu;
     z.pages_out = pages_out;
     z.pages_in = pages_in;
@@ -750,10 +792,11 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
 
 hipError_t launch_rank(const PlanArgs& a, hipStream_t s) {
   static_assert(1024 * 4 == (int)MORI_MAX_PROGRAMS, "the large shape holds every program");
-  // workgroup 0 ranks; the others (about four pages per thread) set up the page state
+  // workgroup 0 ranks; the others (about two table entries per thread) find the
+  // pages' owners
   auto grid = [&](uint32_t rt) {
-    const uint64_t g = ((uint64_t)a.NB + 4ull * rt - 1) / (4ull * rt);
-    return dim3(1 + (uint32_t)(g < 1024 ? g : 1024));
+    const uint64_t g = ((uint64_t)a.tbl_len + 2ull * rt - 1) / (2ull * rt);
+    return dim3(1 + (uint32_t)(g < 2048 ? g : 2048));
   };
   if (a.P <= 64) hipLaunchKernelGGL((rank_partition_kernel<64, 1>), grid(64), dim3(64), 0, s, a);
   else if (a.P <= 256) hipLaunchKernelGGL((rank_partition_kernel<256, 1>), grid(256), dim3(256), 0, s, a);
