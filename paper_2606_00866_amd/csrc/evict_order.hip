@@ -42,9 +42,9 @@
 //
 // The workspace is the caller's, so nothing is allocated here.
 #include <algorithm>
-#include <type_traits>
 
 #include "mori_internal.h"
+#include "sort.h"
 #include "wave.h"
 
 namespace mori {
@@ -888,42 +888,6 @@ __global__ __launch_bounds__(BT) void evict_partition_kernel(BucketArgs a) {
   }
 }
 
-__device__ inline bool pair_less(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
-  return ka < kb || (ka == kb && ia < ib);
-}
-
-// Order of two entries of a bucket being sorted: PACKED ones are single words
-// (key above the bucket's least, then id), the others (key, id) pairs.
-template <bool PACKED>
-__device__ inline bool entry_less(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
-  return PACKED ? ka < kb : pair_less(ka, ia, kb, ib);
-}
-
-// A wave's 64 entries ascending by lane: a bitonic network.
-template <bool PACKED>
-__device__ inline void sort_wave(uint64_t& key, uint32_t& id) {
-  const uint32_t lane = threadIdx.x & 63;
-  auto step = [&](auto D, uint32_t size) {
-    constexpr uint32_t d = decltype(D)::value;
-    const uint64_t k = wave::swap_lanes<d>(key);
-    const uint32_t i = PACKED ? 0u : wave::swap_lanes<d>(id);
-    const bool low = (lane & d) == 0, up = (lane & size) == 0;
-    if (entry_less<PACKED>(k, i, key, id) == (low == up)) {
-      key = k;
-      if (!PACKED) id = i;
-    }
-  };
-#pragma unroll
-  for (uint32_t size = 2; size <= 64; size <<= 1) {
-    if (size >= 64) step(std::integral_constant<uint32_t, 32>(), size);
-    if (size >= 32) step(std::integral_constant<uint32_t, 16>(), size);
-    if (size >= 16) step(std::integral_constant<uint32_t, 8>(), size);
-    if (size >= 8) step(std::integral_constant<uint32_t, 4>(), size);
-    if (size >= 4) step(std::integral_constant<uint32_t, 2>(), size);
-    step(std::integral_constant<uint32_t, 1>(), size);
-  }
-}
-
 // Sorts the bucket's n entries (this thread's: key[it], id[it] at it * BT + tid,
 // padded to m, a multiple of 64, with entries above every real one) into s_key
 // (and s_id unless PACKED): waves sort 64 entries each in registers, then
@@ -948,18 +912,9 @@ __device__ inline void sort_bucket(uint64_t (&key)[BUCKET_IPT], uint32_t (&id)[B
     for (int it = 0; it < BUCKET_IPT; ++it) {
       const uint32_t x = it * BT + tid;
       if (x >= m) break;
-      const uint32_t own = x & ~(L - 1), sib = own ^ L;
       key[it] = s_key[x];
       if (!PACKED) id[it] = s_id[x];
-      uint32_t lo = 0, hi = sib < m ? min(L, m - sib) : 0u;  // entries of the sibling list below this one (none equal)
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        const uint64_t k = s_key[sib + mid];
-        const bool lt = PACKED ? k < key[it] : k < key[it] || (k == key[it] && s_id[sib + mid] < id[it]);
-        if (lt) lo = mid + 1;
-        else hi = mid;
-      }
-      to[it] = min(own, sib) + (x - own) + lo;
+      to[it] = merged_place<PACKED>(s_key, s_id, m, L, x, key[it], id[it]);
     }
     __syncthreads();
 #pragma unroll

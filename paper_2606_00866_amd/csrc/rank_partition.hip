@@ -2,9 +2,9 @@
 //
 //   1. idleness of every program by Eq. 1 (Sec. 4.2), binary32, totals
 //      accumulated oldest cycle first from +0, correctly rounded division;
-//   2. a 64-bit key per program and a stable sort of (key, id): direct rank
-//      counting for up to 256 programs, else an LSD radix sort with wave64
-//      ballots.  Boundary policy: the key is the idleness bits,
+//   2. a 64-bit key per program and a stable sort of (key, id): up to 1024
+//      programs sorted waves merged two by two, above an LSD radix sort with
+//      wave64 ballots.  Boundary policy: the key is the idleness bits,
 //      optionally with the Acting bit of the demotion order of Sec. 4.3.1 --
 //      the relative ranking, busiest first.  Incremental policy (Sec. 4.3.1):
 //      the key is the program's listing group (old tier; Waiting split into
@@ -16,55 +16,58 @@
 //      busiest end) or the greedy skip-fit walk, or the incremental policy:
 //      demote-until-fits is the tail of a tier group past its longest fitting
 //      prefix, promote-while-fits a prefix of the candidates' byte scan;
-//      victims that do not all fit the CPU room and skip-fit promotion are
-//      walked one by one by one thread;
+//      victims that do not all fit the CPU room, skip-fit promotion and the
+//      skip-fit walk go 64 at a time by one wave;
 //   4. the sticky diff (Sec. 4.3): per-program transition category, the
 //      swap-out and swap-in lists in that order and the page/slot bases.
 //
 // P <= 4096 programs fit in LDS (4 keys per thread), so the whole step is one
-// launch: microseconds for tens of programs, about thirty for 4096, bound by
+// launch: 5 us for tens of programs, 7 for 256, about thirty for 4096, bound by
 // the one workgroup's vector ALU and barriers; nothing here is bandwidth-bound.
 #include "mori_internal.h"
+#include "sort.h"
 #include "wave.h"
 
 namespace mori {
 namespace {
 
 // Four shapes, chosen by P at launch: one wave (64 threads, so every barrier
-// is a single wave's) for P <= 64, 256 threads x 1 item up to 256 (ranks
-// counted directly in both), 1024 x 1 up to 1024 and
+// is a single wave's) for P <= 64, 256 threads x 1 item up to 256, 1024 x 1 up
+// to 1024 (all three sorted by merging) and
 // 1024 threads x 4 items (striped: item x = it * RT + tid) up to 4096; fewer
 // item slices mean fewer ballots per radix pass.
 constexpr int RADIX_BITS = 8;
 constexpr int RADIX = 1 << RADIX_BITS;
 constexpr int KEY_BITS = 64;
+constexpr int ID_BITS = 12;      // a program id
 constexpr int GROUP_SHIFT = 61;  // incremental keys: listing group in the top three bits
 // Exclusive scans of the IPT x RT items in rank order (item it of thread tid
 // has rank it * RT + tid), N values per item side by side: wave scans, the
 // per-(slice, wave) totals scanned by the first wave, and three barriers in
-// all, however many slices.  s_tot needs (IPT * NW + 1) * N entries; total[n]
-// receives the sum of value n over all items.
+// all, however many slices.  Blocks and programs, whose totals a table's 32-bit
+// offsets bound: a 32-bit step is one instruction where a 64-bit one is four.
+// s_tot needs (IPT * NW + 1) * N entries; total[n] receives the sum of value n
+// over all items.
 template <int NW, int IPT, int N>
-__device__ void scan_slices(const uint64_t (&v)[IPT][N], uint64_t (&ex)[IPT][N], uint64_t* s_tot,
-                            uint64_t (&total)[N]) {
+__device__ void scan_slices(const uint32_t (&v)[IPT][N], uint32_t (&ex)[IPT][N], uint32_t* s_tot,
+                            uint32_t (&total)[N]) {
   constexpr int NS = IPT * NW;
   static_assert(NS <= 64, "one lane per (slice, wave) total");
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  uint64_t inc[IPT][N];
 #pragma unroll
   for (int it = 0; it < IPT; ++it)
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-      const uint64_t x = wave::incl_add(v[it][n]);
-      inc[it][n] = x;
+      const uint32_t x = wave::incl_add(v[it][n]);
+      ex[it][n] = x - v[it][n];
       if (lane == 63) s_tot[(it * NW + wid) * N + n] = x;
     }
   __syncthreads();
   if (wid == 0) {
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-      const uint64_t w = lane < NS ? s_tot[lane * N + n] : 0ull;
-      const uint64_t wi = wave::incl_add(w);
+      const uint32_t w = lane < NS ? s_tot[lane * N + n] : 0u;
+      const uint32_t wi = wave::incl_add(w);
       if (lane < NS) s_tot[lane * N + n] = wi - w;
       if (lane == NS - 1) s_tot[NS * N + n] = wi;
     }
@@ -73,7 +76,7 @@ __device__ void scan_slices(const uint64_t (&v)[IPT][N], uint64_t (&ex)[IPT][N],
 #pragma unroll
   for (int it = 0; it < IPT; ++it)
 #pragma unroll
-    for (int n = 0; n < N; ++n) ex[it][n] = s_tot[(it * NW + wid) * N + n] + inc[it][n] - v[it][n];
+    for (int n = 0; n < N; ++n) ex[it][n] += s_tot[(it * NW + wid) * N + n];
 #pragma unroll
   for (int n = 0; n < N; ++n) total[n] = s_tot[NS * N + n];
   __syncthreads();
@@ -85,11 +88,6 @@ __device__ inline void add_to(uint32_t* dst, uint32_t v) {
   const uint32_t t = wave::sum(v);
   if ((threadIdx.x & 63) == 0 && t) atomicAdd(dst, t);
 }
-__device__ inline void add_to(unsigned long long* dst, uint64_t v) {
-  const uint64_t t = wave::sum(v);
-  if ((threadIdx.x & 63) == 0 && t) atomicAdd(dst, (unsigned long long)t);
-}
-
 // Largest p in [0, P) with off[p] <= e (so off[p] <= e < off[p+1] when e < off[P]).
 __device__ inline uint32_t find_program(const uint32_t* off, uint32_t P, uint32_t e) {
   uint32_t lo = 0, hi = P;  // invariant: off[lo] <= e, answer in [lo, hi)
@@ -128,6 +126,70 @@ __device__ void claim_pages(const PlanArgs& a, uint32_t b, uint32_t nb) {
   if (err) atomicOr(a.page_err, err);
 }
 
+// Sorts one (key, id) per thread, padded above P programs: entries 0 .. P - 1
+// (and the padding to a multiple of 64) end up ascending in s_key (and s_id
+// unless PACKED).
+template <bool PACKED>
+__device__ void sort_programs(uint64_t key, uint32_t id, uint32_t P, uint64_t* s_key, uint32_t* s_id) {
+  const uint32_t m = (P + 63) & ~63u;
+  const uint32_t x = threadIdx.x;
+  const bool active = x < m;  // whole waves
+  if (active) {
+    sort_wave<PACKED>(key, id, P);
+    s_key[x] = key;
+    if (!PACKED) s_id[x] = id;
+  }
+  __syncthreads();
+  for (uint32_t L = 64; L < m; L <<= 1) {
+    uint32_t to = 0;
+    if (active) {
+      key = s_key[x];
+      if (!PACKED) id = s_id[x];
+      to = merged_place<PACKED>(s_key, s_id, m, L, x, key, id);
+    }
+    __syncthreads();
+    if (active) {
+      s_key[to] = key;
+      if (!PACKED) s_id[to] = id;
+    }
+    __syncthreads();
+  }
+}
+
+// Skip-fit over 64 candidates in lane order: each is taken if it still fits the
+// room left when its turn comes.  b: this lane's blocks; pending: the
+// candidates; returns those taken and lowers room (blocks).  A round takes the
+// longest run that fits together: the candidate after it, and any that is
+// larger than the room left, can never be taken.  All lanes call it.
+__device__ inline uint64_t take_fitting(uint64_t pending, uint64_t b, uint64_t& room) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint64_t taken = 0;
+  for (;;) {
+    pending &= __ballot(b <= room);
+    if (!pending) return taken;
+    const uint64_t sum = wave::incl_add<uint64_t>((pending >> lane) & 1u ? b : 0u);
+    const uint64_t fits = pending & __ballot(sum <= room);  // a run: the sums never decrease, and the first one fits
+    room -= wave::lane_of(sum, 63 - __builtin_clzll(fits));
+    taken |= fits;
+    pending &= ~fits;
+  }
+}
+
+// Skip-fit over ranks [lo, hi) (in reverse: hi - 1 down to lo) by one wave:
+// those taken go to `tier`.  One thread over the ranks took 0.1 us a program
+// (incremental skip-fit, 1024 programs 7.2 us).
+template <bool REVERSE>
+__device__ void walk_fit(const uint32_t* blocks, uint8_t* tiers, uint32_t lo, uint32_t hi, uint64_t& room,
+                         uint8_t tier) {
+  const uint32_t lane = threadIdx.x & 63;
+  for (uint32_t c = lo; c < hi; c += 64) {
+    const bool valid = c + lane < hi;
+    const uint32_t r = REVERSE ? hi - 1 - (c - lo + lane) : c + lane;
+    const uint64_t taken = take_fitting(__ballot(valid), valid ? blocks[r] : 0u, room);
+    if ((taken >> lane) & 1u) tiers[r] = tier;
+  }
+}
+
 // Transition category.  Leaving the GPU for a tier that keeps the KV (CPU,
 // SSD) is a swap-out, the reverse a swap-in.
 __device__ inline uint8_t category(uint8_t from, uint8_t to) {
@@ -158,13 +220,13 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   __shared__ uint8_t s_tier[RT * IPT];
   __shared__ uint32_t s_nblk[RT * IPT];  // blocks of program x
   __shared__ uint8_t s_told[RT * IPT];   // old tier of program x
-  __shared__ uint64_t s_tot[(IPT * NW + 1) * 3];
+  __shared__ uint32_t s_tot[(IPT * NW + 1) * 5];
   __shared__ uint32_t s_w32[NW + 1];
   __shared__ unsigned long long s_or, s_and;
   __shared__ uint32_t s_err, s_m_gpu, s_m_cpu, s_m_ssd;
   __shared__ uint32_t s_grp[5], s_cpu_reasoning, s_k_gpu, s_k_cpu;
-  __shared__ uint32_t s_n_drop_gpu, s_n_drop_cpu, s_n_admit_cpu;
-  __shared__ unsigned long long s_gpu_after, s_cpu_after, s_ssd_after, s_gpu_part, s_upper_part;
+  __shared__ uint32_t s_n_drop, s_n_admit_cpu, s_gpu_after, s_cpu_after, s_ssd_after;
+  __shared__ unsigned long long s_gpu_part, s_upper_part;
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   if (blockIdx.x > 0) {  // the other workgroups find the pages' owners meanwhile
@@ -182,7 +244,7 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     s_m_gpu = s_m_cpu = s_m_ssd = 0;
     for (int g = 0; g < 5; ++g) s_grp[g] = 0;
     s_cpu_reasoning = s_k_gpu = s_k_cpu = 0;
-    s_n_drop_gpu = s_n_drop_cpu = s_n_admit_cpu = 0;
+    s_n_drop = s_n_admit_cpu = 0;
     s_gpu_after = s_cpu_after = s_ssd_after = 0;
     s_gpu_part = s_upper_part = 0;
   }
@@ -210,14 +272,14 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     const uint8_t told = a.tier[x];
     const uint32_t off0 = a.tbl_off[x], off1 = a.tbl_off[x + 1];
     const uint8_t st = need_status ? a.status[x] : 0;
-    float rv[8], cv[8];  // the first eight cycles of the window (clamped indices: k >= 1)
+    float rv[8], cv[8];  // the first eight cycles of the window
     const float* w = given ? nullptr : a.window + (size_t)x * a.k * 2;
     if (!given) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const uint32_t j = min((uint32_t)u, a.k - 1);
-        rv[u] = w[2 * j];
-        cv[u] = w[2 * j + 1];
+        if ((uint32_t)u >= a.k) break;  // uniform
+        rv[u] = w[2 * u];
+        cv[u] = w[2 * u + 1];
       }
     }
     if (told > top_tier) err |= MORI_DEV_BAD_TIER;
@@ -287,7 +349,7 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     if (lane == 0 && w_and != ~0ull) atomicAnd(&s_and, (unsigned long long)w_and);
   }
   if (err) atomicOr(&s_err, err);
-  if constexpr (!(IPT == 1 && RT <= 256)) {  // the first radix pass's digit counters
+  if constexpr (IPT > 1) {  // the first radix pass's digit counters
 #pragma unroll
     for (int j = 0; j < CPT; ++j) s_cnt[cidx(j * RT + tid)] = 0;
   }
@@ -323,34 +385,22 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   }
 
   // ---- 2. stable sort of (key, id) ---------------------------------------
-  if constexpr (IPT == 1 && RT <= 256) {
-    // P <= 256: each program's rank is the number of programs before it in
-    // (key, id) order, counted against every key in LDS (the same address for
-    // all lanes, a broadcast): P steps and four barriers, where the radix sort
-    // takes up to sixteen passes of several barriers and a workgroup scan each.
-    s_key[tid] = key[0];
-    __syncthreads();
-    uint32_t rank = tid;  // padding keeps its slot: every real rank is below P
-    if ((uint32_t)tid < P) {
-      // eight keys' loads in flight per step; the padding keys past P (all
-      // ones, above every real key) count for nobody
-      const uint64_t k = key[0];
-      const uint32_t P8 = (P + 7u) & ~7u;
-      rank = 0;
-      for (uint32_t j0 = 0; j0 < P8; j0 += 8) {
-        uint64_t kj[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) kj[u] = s_key[j0 + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) rank += (kj[u] < k) | ((kj[u] == k) & (j0 + u < (uint32_t)tid));
-      }
+  if constexpr (IPT == 1) {
+    // P <= 1024: one program a thread, waves sorted and lists merged in LDS.
+    // Boundary keys, and incremental ones of less than 2^20 blocks, leave room
+    // for the id in the same word.  (Counting ranks against keys in LDS took
+    // 7.1 us at 256 programs, radix passes 5.2 us at 1024 and 7.6 us with
+    // incremental keys; this 2.0 and 4.3 us.)
+    const uint32_t x = tid;
+    if ((kor >> (64 - ID_BITS)) == 0) {
+      sort_programs<true>(x < P ? (key[0] << ID_BITS) | x : ~0ull, x, P, s_key, s_id);
+      key[0] = s_key[tid] >> ID_BITS;
+      id[0] = (uint32_t)s_key[tid] & ((1u << ID_BITS) - 1u);
+    } else {
+      sort_programs<false>(key[0], id[0], P, s_key, s_id);
+      key[0] = s_key[tid];
+      id[0] = s_id[tid];
     }
-    __syncthreads();
-    s_key[rank] = key[0];
-    s_id[rank] = id[0];
-    __syncthreads();
-    key[0] = s_key[tid];
-    id[0] = s_id[tid];
     __syncthreads();
   } else {
     // LSD radix sort, 8-bit digits (at most four passes over idleness keys).
@@ -452,13 +502,13 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   // ---- 3. KV-byte prefix in that order and the placement ----------------
   uint64_t S[IPT];
   {
-    uint64_t bytes[IPT][1], ex[IPT][1], tot[1];
+    uint32_t blocks[IPT][1], ex[IPT][1], tot[1];
 #pragma unroll
-    for (int it = 0; it < IPT; ++it) bytes[it][0] = (uint64_t)nb[it] * a.block_bytes;
-    scan_slices<NW, IPT, 1>(bytes, ex, s_tot, tot);
+    for (int it = 0; it < IPT; ++it) blocks[it][0] = nb[it];
+    scan_slices<NW, IPT, 1>(blocks, ex, s_tot, tot);
 #pragma unroll
     for (int it = 0; it < IPT; ++it) {
-      S[it] = ex[it][0] + bytes[it][0];
+      S[it] = (uint64_t)(ex[it][0] + nb[it]) * a.block_bytes;
       s_key[it * RT + tid] = S[it];
     }
   }
@@ -513,45 +563,31 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     }
     // (3) promotion: a strict prefix of the candidates' byte scan
     if (!(a.flags & MORI_F_SKIP_FIT)) {
-      uint64_t cb[IPT][1], ex[IPT][1], tot[1];
+      uint32_t cb[IPT][1], ex[IPT][1], tot[1];
       bool cand[IPT];
 #pragma unroll
       for (int it = 0; it < IPT; ++it) {
         const uint32_t r = it * RT + tid;
         cand[it] = (r >= g1 && r < c_end) || (r >= g2 && r < g4);
-        cb[it][0] = cand[it] ? (uint64_t)nb[it] * a.block_bytes : 0;
+        cb[it][0] = cand[it] ? nb[it] : 0u;
       }
       scan_slices<NW, IPT, 1>(cb, ex, s_tot, tot);
 #pragma unroll
       for (int it = 0; it < IPT; ++it)
-        if (cand[it] && ex[it][0] + cb[it][0] <= room_gpu) s_tier[it * RT + tid] = MORI_TIER_GPU;
+        if (cand[it] && (uint64_t)(ex[it][0] + cb[it][0]) * a.block_bytes <= room_gpu) s_tier[it * RT + tid] = MORI_TIER_GPU;
     }
     __syncthreads();
-    if (tid == 0) {
-      if (!victims_fit) {  // each victim, most demotable first, to the CPU tier if it still fits
-        uint64_t room = room_cpu;
-        for (uint32_t r = g1; r-- > k_gpu;) {
-          const uint64_t b = (uint64_t)s_id[r] * a.block_bytes;
-          if (b <= room) {
-            room -= b;
-            s_tier[r] = MORI_TIER_CPU;
-          } else {
-            s_tier[r] = MORI_TIER_WAIT;
-          }
-        }
+    if (wid == 0) {
+      // each victim, most demotable first, to the CPU tier if it still fits
+      if (!victims_fit) {
+        uint64_t room = room_cpu / a.block_bytes;
+        walk_fit<true>(s_id, s_tier, k_gpu, g1, room, MORI_TIER_CPU);
       }
       if (a.flags & MORI_F_SKIP_FIT) {
-        uint64_t room = room_gpu;
-        for (int part = 0; part < 2; ++part) {
-          const uint32_t lo = part ? g2 : g1, hi = part ? g4 : c_end;
-          for (uint32_t r = lo; r < hi; ++r) {
-            const uint64_t b = (uint64_t)s_id[r] * a.block_bytes;
-            if (b <= room) {
-              room -= b;
-              s_tier[r] = MORI_TIER_GPU;
-            }
-          }
-        }
+        // the returning programs and new arrivals go on with the room the CPU programs left
+        uint64_t room = room_gpu / a.block_bytes;
+        walk_fit<false>(s_id, s_tier, g1, c_end, room, MORI_TIER_GPU);
+        walk_fit<false>(s_id, s_tier, g2, g4, room, MORI_TIER_GPU);
       }
     }
     __syncthreads();
@@ -614,48 +650,51 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
                 : r < upper + m_ssd ? MORI_TIER_SSD : MORI_TIER_WAIT;
     }
   } else {
-    // Greedy walk in rank order: first tier that still has room.
+    // Greedy in rank order: the first tier that still has room.  Whether a
+    // program fits a tier depends on that tier's room alone, so 64 ranks at a
+    // time are offered to each tier in turn.
     __syncthreads();
-    if (tid == 0) {
-      uint64_t room_gpu = a.gpu_bytes, room_cpu = a.cpu_bytes, room_ssd = a.ssd_bytes;
+    if (wid == 0) {
+      uint64_t room_gpu = a.gpu_bytes / a.block_bytes, room_cpu = a.cpu_bytes / a.block_bytes;
+      uint64_t room_ssd = a.ssd_bytes / a.block_bytes;
       uint32_t ng = 0, nc = 0, ns = 0;
-      for (uint32_t r = 0; r < P; ++r) {
-        const uint64_t bytes = (uint64_t)s_id[r] * a.block_bytes;
-        if (bytes <= room_gpu) {
-          room_gpu -= bytes;
-          s_tier[r] = MORI_TIER_GPU;
-          ++ng;
-        } else if (bytes <= room_cpu) {
-          room_cpu -= bytes;
-          s_tier[r] = MORI_TIER_CPU;
-          ++nc;
-        } else if (ssd && bytes <= room_ssd) {
-          room_ssd -= bytes;
-          s_tier[r] = MORI_TIER_SSD;
-          ++ns;
-        } else {
-          s_tier[r] = MORI_TIER_WAIT;
-        }
+      for (uint32_t c = 0; c < P; c += 64) {
+        const bool valid = c + lane < P;
+        const uint64_t b = valid ? s_id[c + lane] : 0u;
+        const uint64_t all = __ballot(valid);
+        const uint64_t gpu = take_fitting(all, b, room_gpu);
+        const uint64_t cpu = take_fitting(all & ~gpu, b, room_cpu);
+        const uint64_t sd = ssd ? take_fitting(all & ~(gpu | cpu), b, room_ssd) : 0ull;
+        if (valid)
+          s_tier[c + lane] = (gpu >> lane) & 1u ? MORI_TIER_GPU
+                           : (cpu >> lane) & 1u ? MORI_TIER_CPU
+                           : (sd >> lane) & 1u ? MORI_TIER_SSD : MORI_TIER_WAIT;
+        ng += (uint32_t)__popcll(gpu);
+        nc += (uint32_t)__popcll(cpu);
+        ns += (uint32_t)__popcll(sd);
       }
-      s_m_gpu = ng;
-      s_m_cpu = nc;
-      s_m_ssd = ns;
+      if (lane == 0) {
+        s_m_gpu = ng;
+        s_m_cpu = nc;
+        s_m_ssd = ns;
+      }
     }
   }
   __syncthreads();
 
   // ---- 4. sticky diff: categories, lists in rank order, bases -----------
-  // packed scans: A = pages_out | pages_in << 32, B = pages_admit | n_out << 32 | n_in << 48, and n_admit_gpu
+  // scans: pages_out, pages_in, pages_admit, n_out | n_in << 16, n_admit_gpu
   // Global stores wait until after the last barrier: a barrier waits for the
   // stores still in flight, so stores issued earlier would stall every one.
-  uint64_t vab[IPT][3], exab[IPT][3], totab[3];
+  uint32_t v[IPT][5], ex[IPT][5], tot[5];
   uint8_t catv[IPT], tnewv[IPT];
-  uint32_t n_dg = 0, n_dc = 0, n_ac = 0;
-  uint64_t gpu_after = 0, cpu_after = 0, ssd_after = 0;
+  uint32_t n_drop = 0, n_ac = 0;  // dropped: from the GPU | from the CPU << 16
+  uint32_t gpu_after = 0, cpu_after = 0, ssd_after = 0;  // blocks
 #pragma unroll
   for (int it = 0; it < IPT; ++it) {
     const uint32_t r = it * RT + tid;
-    uint64_t va = 0, vb = 0, vc = 0;
+#pragma unroll
+    for (int n = 0; n < 5; ++n) v[it][n] = 0;
     catv[it] = MORI_CAT_KEPT;
     if (r < P) {
       const uint32_t p = id[it];
@@ -663,26 +702,20 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
       const uint8_t c = category(told, tnew);
       catv[it] = c;
       tnewv[it] = tnew;
-      if (c == MORI_CAT_OUT) va = nb[it], vb = 1ull << 32;
-      if (c == MORI_CAT_IN) va = (uint64_t)nb[it] << 32, vb = 1ull << 48;
-      if (c == MORI_CAT_ADMIT_GPU) vb = nb[it], vc = 1;
-      if (c == MORI_CAT_DROP_GPU) ++n_dg;
-      if (c == MORI_CAT_DROP_CPU) ++n_dc;
+      if (c == MORI_CAT_OUT) v[it][0] = nb[it], v[it][3] = 1u;
+      if (c == MORI_CAT_IN) v[it][1] = nb[it], v[it][3] = 1u << 16;
+      if (c == MORI_CAT_ADMIT_GPU) v[it][2] = nb[it], v[it][4] = 1u;
+      if (c == MORI_CAT_DROP_GPU) n_drop += 1u;
+      if (c == MORI_CAT_DROP_CPU) n_drop += 1u << 16;
       if (c == MORI_CAT_ADMIT_CPU) ++n_ac;
-      if (tnew == MORI_TIER_GPU) gpu_after += (uint64_t)nb[it] * a.block_bytes;
-      if (tnew == MORI_TIER_CPU) cpu_after += (uint64_t)nb[it] * a.block_bytes;
-      if (tnew == MORI_TIER_SSD) ssd_after += (uint64_t)nb[it] * a.block_bytes;
+      if (tnew == MORI_TIER_GPU) gpu_after += nb[it];
+      if (tnew == MORI_TIER_CPU) cpu_after += nb[it];
+      if (tnew == MORI_TIER_SSD) ssd_after += nb[it];
     }
-    vab[it][0] = va;
-    vab[it][1] = vb;
-    vab[it][2] = vc;
   }
-  scan_slices<NW, IPT, 3>(vab, exab, s_tot, totab);
-  const uint64_t carryA = totab[0], carryB = totab[1];
-  const uint32_t pages_out = (uint32_t)(carryA & 0xFFFFFFFFu), pages_in = (uint32_t)(carryA >> 32);
-  const uint32_t pages_admit = (uint32_t)(carryB & 0xFFFFFFFFu);
-  const uint32_t n_out = (uint32_t)((carryB >> 32) & 0xFFFFu), n_in = (uint32_t)(carryB >> 48);
-  const uint32_t n_admit = (uint32_t)totab[2];
+  scan_slices<NW, IPT, 5>(v, ex, s_tot, tot);
+  const uint32_t pages_out = tot[0], pages_in = tot[1], pages_admit = tot[2];
+  const uint32_t n_out = tot[3] & 0xFFFFu, n_in = tot[3] >> 16, n_admit = tot[4];
   // program-indexed staging, so the per-program stores below are coalesced:
   // the new tier and the page base by program id (every read of the
   // rank-indexed s_tier and s_nblk came before the scan's first barrier)
@@ -691,18 +724,16 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     const uint32_t r = it * RT + tid;
     if (r >= P) continue;
     const uint32_t p = id[it];
-    const uint64_t exA = exab[it][0], exB = exab[it][1];
     s_tier[p] = tnewv[it];
-    if (catv[it] == MORI_CAT_OUT) s_nblk[p] = (uint32_t)(exA & 0xFFFFFFFFu);
-    if (catv[it] == MORI_CAT_IN) s_nblk[p] = (uint32_t)(exA >> 32);
-    if (catv[it] == MORI_CAT_ADMIT_GPU) s_nblk[p] = pages_in + (uint32_t)(exB & 0xFFFFFFFFu);
+    if (catv[it] == MORI_CAT_OUT) s_nblk[p] = ex[it][0];
+    if (catv[it] == MORI_CAT_IN) s_nblk[p] = ex[it][1];
+    if (catv[it] == MORI_CAT_ADMIT_GPU) s_nblk[p] = pages_in + ex[it][2];
   }
-  add_to(&s_n_drop_gpu, n_dg);
-  add_to(&s_n_drop_cpu, n_dc);
+  add_to(&s_n_drop, n_drop);
   add_to(&s_n_admit_cpu, n_ac);
   add_to(&s_gpu_after, gpu_after);
   add_to(&s_cpu_after, cpu_after);
-  add_to(&s_ssd_after, ssd_after);
+  if (ssd) add_to(&s_ssd_after, ssd_after);
   __syncthreads();
 
   // ---- 5. the plan's stores ------------------------------------------------
@@ -716,10 +747,9 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     a.prefix[r] = S[it];
     *host_mirror(a, a.order + r) = p;
     *host_mirror(a, a.prefix + r) = S[it];
-    const uint64_t exA = exab[it][0], exB = exab[it][1];
-    const uint32_t idx_out = (uint32_t)((exB >> 32) & 0xFFFFu), idx_in = (uint32_t)(exB >> 48);
+    const uint32_t idx_out = ex[it][3] & 0xFFFFu, idx_in = ex[it][3] >> 16;
     if (catv[it] == MORI_CAT_OUT) {
-      const uint32_t pg = (uint32_t)(exA & 0xFFFFFFFFu);
+      const uint32_t pg = ex[it][0];
       a.ord[p] = idx_out;
       a.out_prog[idx_out] = p;
       a.out_pg_base[idx_out] = pg;
@@ -727,7 +757,7 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
       *host_mirror(a, a.out_pg_base + idx_out) = pg;
     }
     if (catv[it] == MORI_CAT_IN) {  // programs promoted from the CPU (or SSD) tier take the first slots (Sec. 4.3.1)
-      const uint32_t pg = (uint32_t)(exA >> 32);
+      const uint32_t pg = ex[it][1];
       a.ord[p] = idx_in;
       a.in_prog[idx_in] = p;
       a.in_pg_base[idx_in] = pg;
@@ -737,8 +767,8 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
       *host_mirror(a, a.in_pg_base + idx_in) = pg;
     }
     if (catv[it] == MORI_CAT_ADMIT_GPU) {  // then the programs admitted from Waiting: priority (2)
-      const uint32_t idx = n_in + (uint32_t)exab[it][2];
-      a.slot_base[idx] = pages_in + (uint32_t)(exB & 0xFFFFFFFFu);
+      const uint32_t idx = n_in + ex[it][4];
+      a.slot_base[idx] = pages_in + ex[it][2];
       a.slot_prog[idx] = p;
     }
   }
@@ -770,8 +800,8 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     z.m_ssd = s_m_ssd;
     z.n_out = n_out;
     z.n_in = n_in;
-    z.n_drop_gpu = s_n_drop_gpu;
-    z.n_drop_cpu = s_n_drop_cpu;
+    z.n_drop_gpu = s_n_drop & 0xFFFFu;
+    z.n_drop_cpu = s_n_drop >> 16;
     z.n_admit_gpu = n_admit;
     z.n_admit_cpu = s_n_admit_cpu;
     z.pages_out = pages_out;
@@ -779,9 +809,9 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     z.pages_admit = pages_admit;
     z.bytes_out = (uint64_t)pages_out * a.block_bytes;
     z.bytes_in = (uint64_t)pages_in * a.block_bytes;
-    z.gpu_bytes_after = s_gpu_after;
-    z.cpu_bytes_after = s_cpu_after;
-    z.ssd_bytes_after = s_ssd_after;
+    z.gpu_bytes_after = (uint64_t)s_gpu_after * a.block_bytes;
+    z.cpu_bytes_after = (uint64_t)s_cpu_after * a.block_bytes;
+    z.ssd_bytes_after = (uint64_t)s_ssd_after * a.block_bytes;
     z.need = (uint64_t)pages_in + pages_admit;
     *a.sum = z;
     a.swap_err[0] = a.swap_err[1] = 0;

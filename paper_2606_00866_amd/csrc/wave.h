@@ -56,6 +56,12 @@ __device__ inline uint64_t lane63(uint64_t v) {
   return ((uint64_t)lane63((uint32_t)(v >> 32)) << 32) | lane63((uint32_t)v);
 }
 
+// v of one lane (the same for the whole wavefront), as a wave-uniform value.
+__device__ inline uint64_t lane_of(uint64_t v, int lane) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+}
+
 // Totals over the wavefront, the same (wave-uniform) value in every lane.
 template <typename T>
 __device__ inline T sum(T v) { return lane63(incl(v, Add())); }
