@@ -929,9 +929,10 @@ __device__ inline void sort_bucket(uint64_t (&key)[BUCKET_IPT], uint32_t (&id)[B
 }
 
 // One bucket per workgroup, sorted in LDS and written out with the prefix.
-// Where the bucket's keys span less than 2^44 (all but the few buckets that
-// hold two types, in practice), key and id fit one word: one compare and two
-// registers an entry instead of three and three.  A bucket of more than
+// Where the bucket's keys span less than 2^44 - 1 (all but the few buckets that
+// hold two types, in practice), key and id fit one word below the padding's:
+// one compare and two registers an entry instead of three and three (an entry
+// equal to the padding would share a place with it in a merge).  A bucket of more than
 // BUCKET_CAP blocks, which only a sample that misses the distribution leaves,
 // is ranked by counting, in which all workgroups share.
 __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(8))) void evict_bucket_kernel(BucketArgs a) {
@@ -982,7 +983,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(8))) void ev
     if (x >= m) break;
     key[it] = x < n ? a.key[first + x] : ~0ull;
     id[it] = x < n ? a.id[first + x] : ~0u;
-    wide |= x < n && ((key[it] - least) >> (64 - BUCKET_ID_BITS)) != 0;
+    wide |= x < n && ((key[it] - least + 1) >> (64 - BUCKET_ID_BITS)) != 0;
   }
   __syncthreads();  // s_wide is zero
   if (wide) s_wide = 1;

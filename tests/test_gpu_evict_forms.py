@@ -69,6 +69,17 @@ def test_bucket_larger_than_lds(var_size):
     check(np.ones(N, np.uint8), la, size, 3, 1, 3 * (N // 2))
 
 
+@pytest.mark.parametrize("span", [(1 << 44) - 2, (1 << 44) - 1, 1 << 44])
+def test_packing_limit(span):
+    """The last of 2^20 blocks, all others of one time, is `span` newer: at
+    2^44 - 1 its key and id in one word would equal the bucket's padding."""
+    N = 1 << 20
+    la = np.full(N, 99, np.uint64)
+    la[N - 1] = 99 + span
+    log(f"evict span={span}")
+    check(np.zeros(N, np.uint8), la, None, 16, 0, 16 * (N - 1) + 1)
+
+
 @pytest.mark.parametrize("N", [3000, 50000])
 def test_invalid_block_and_no_prefix(N):
     rng = np.random.default_rng(N)
