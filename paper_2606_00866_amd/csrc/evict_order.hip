@@ -521,60 +521,6 @@ __global__ void evict_result_kernel(EvictArgs a) {
 
 // ---- direct and bucket forms ------------------------------------------------
 
-__device__ inline uint64_t uniform64(uint64_t x) {
-  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
-         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-}
-
-// For E consecutive staged elements i0 .. i0 + E - 1 of one wave (i0 a multiple
-// of E): how many staged keys come before each (lower key, or equal key and
-// lower index) and with BYTES the sum of their sizes.  The keys come in chunks
-// of 64, a multiple of GROUP of them; keys past the last element are all ones.
-// The elements' keys are uniform, so a chunk costs a 64-bit compare against a
-// scalar and an add of the carry per element.  Equal keys come first in lower
-// groups of chunks, where the compare is with key + 1, not in higher ones,
-// where it is with the key, and by index in the elements' own group.
-constexpr uint32_t GROUP = 4;  // chunks whose loads are in flight together
-template <int E, bool BYTES>
-__device__ inline void count_before(const uint64_t* s_key, const uint32_t* s_size, uint32_t chunks, uint32_t i0,
-                                    uint32_t (&rank)[E], uint64_t (&bytes)[E]) {
-  const uint32_t lane = threadIdx.x & 63;
-  uint64_t k[E], sum[E];
-  uint32_t cnt[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    k[e] = uniform64(s_key[i0 + e]);
-    cnt[e] = 0;
-    sum[e] = 0;
-  }
-  auto group = [&](uint32_t c0, auto limit) {
-    uint64_t kj[GROUP];
-    uint32_t sz[GROUP];
-#pragma unroll
-    for (uint32_t g = 0; g < GROUP; ++g) {
-      kj[g] = s_key[(c0 + g) * 64 + lane];
-      sz[g] = BYTES ? s_size[(c0 + g) * 64 + lane] : 0u;
-    }
-#pragma unroll
-    for (uint32_t g = 0; g < GROUP; ++g)
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const bool before = kj[g] < limit(e, (c0 + g) * 64 + lane);
-        cnt[e] += before;
-        if (BYTES) sum[e] += before ? sz[g] : 0u;
-      }
-  };
-  const uint32_t own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(i0 / (64 * GROUP) * GROUP));
-  for (uint32_t c = 0; c < own; c += GROUP) group(c, [&](int e, uint32_t) { return k[e] + 1; });
-  group(own, [&](int e, uint32_t j) { return k[e] + (j < i0 + e); });
-  for (uint32_t c = own + GROUP; c < chunks; c += GROUP) group(c, [&](int e, uint32_t) { return k[e]; });
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    rank[e] = wave::sum(cnt[e]);
-    bytes[e] = BYTES ? wave::sum(sum[e]) : rank[e];
-  }
-}
-
 // One block's entry of the order, its prefix (`through` = bytes freed up to and
 // with it) and, where the prefix first reaches need, the eviction count.
 __device__ inline void emit(const EvictArgs& a, uint32_t rank, uint32_t id, uint64_t through, uint64_t own) {

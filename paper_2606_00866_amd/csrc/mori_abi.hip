@@ -82,6 +82,9 @@ struct mori_ctx {
   uint8_t* blob_host = nullptr;  // pinned mirror
   uint8_t* blob_host_dev = nullptr;  // the mirror as the device addresses it
   uint8_t* scratch = nullptr;    // device-only arrays
+  uint64_t* key = nullptr;
+  uint32_t* key_err = nullptr;
+  uint64_t* rank_rec = nullptr;
   uint32_t* base = nullptr;
   uint64_t* owner = nullptr;
   uint8_t* pcode = nullptr;
@@ -245,6 +248,7 @@ extern "C" int mori_create(const mori_pool* pool, uint32_t max_programs, uint64_
     o += (bytes + 255) & ~size_t(255);
     return r;
   };
+  const size_t o_key = take(8 * pm), o_key_err = take(4 * pm), o_rank_rec = take(8 * pm);
   const size_t o_base = take(4 * pm), o_owner = take(8 * NB), o_pcode = take(NB), o_page_err = take(4);
   const size_t o_slot_base = take(4 * pm), o_slot_prog = take(4 * pm), o_out_src = take(4 * NB), o_in_dst = take(4 * NB);
   const size_t o_ord = take(4 * pm), o_out_ord = take(4 * NB), o_in_ord = take(4 * NB);
@@ -252,6 +256,9 @@ extern "C" int mori_create(const mori_pool* pool, uint32_t max_programs, uint64_
   const size_t o_ad0 = take(8 * pm), o_ad1 = take(8 * pm);
   const size_t o_err = take(8), o_rng = take(sizeof(DevRange) * MORI_MAX_RANGES), o_sr = take(2 * sizeof(SwapRange));
   if ((e = hipMalloc(&c->scratch, o)) != hipSuccess) return fail(e);
+  c->key = reinterpret_cast<uint64_t*>(c->scratch + o_key);
+  c->key_err = reinterpret_cast<uint32_t*>(c->scratch + o_key_err);
+  c->rank_rec = reinterpret_cast<uint64_t*>(c->scratch + o_rank_rec);
   c->base = reinterpret_cast<uint32_t*>(c->scratch + o_base);
   c->owner = reinterpret_cast<uint64_t*>(c->scratch + o_owner);
   c->pcode = c->scratch + o_pcode;
@@ -400,6 +407,9 @@ extern "C" int mori_rank_partition(mori_ctx* ctx, const mori_programs* pr, const
   a.in_prog = ctx->dev<uint32_t>(ctx->L.in_prog);
   a.out_pg_base = ctx->dev<uint32_t>(ctx->L.out_base);
   a.in_pg_base = ctx->dev<uint32_t>(ctx->L.in_base);
+  a.key = ctx->key;
+  a.key_err = ctx->key_err;
+  a.rank_rec = ctx->rank_rec;
   a.base = ctx->base;
   a.owner = ctx->owner;
   a.pcode = ctx->pcode;

@@ -62,6 +62,9 @@ struct PlanArgs {
   uint32_t* out_pg_base;  // [n_out + 1] first out-page index of each out program
   uint32_t* in_pg_base;   // [n_in + 1] first slot of each in program
   // context scratch: device only
+  uint64_t* key;          // per program: its key
+  uint32_t* key_err;      // per 64 programs: what is wrong with their data
+  uint64_t* rank_rec;     // by rank: program and what the placement reads of it
   uint32_t* base;         // per program: out-page base (OUT) or slot base (IN, ADMIT_GPU)
   uint64_t* owner;        // [NB] program << 32 | (table entry + 1) of each owned page, 0 between plans
   uint8_t* pcode;         // [NB] PC_* of each page

@@ -1,10 +1,10 @@
-// Rank / boundary step of one rebalance, in a single workgroup.
+// Rank / boundary step of one rebalance: the placement in a single workgroup.
 //
 //   1. idleness of every program by Eq. 1 (Sec. 4.2), binary32, totals
 //      accumulated oldest cycle first from +0, correctly rounded division;
-//   2. a 64-bit key per program and a stable sort of (key, id): up to 1024
-//      programs sorted waves merged two by two, above an LSD radix sort with
-//      wave64 ballots.  Boundary policy: the key is the idleness bits,
+//   2. a 64-bit key per program and a stable sort of (key, id): sorted waves
+//      merged two by two, or for many programs or long windows ranks counted
+//      by two kernels before this one.  Boundary policy: the key is the idleness bits,
 //      optionally with the Acting bit of the demotion order of Sec. 4.3.1 --
 //      the relative ranking, busiest first.  Incremental policy (Sec. 4.3.1):
 //      the key is the program's listing group (old tier; Waiting split into
@@ -21,9 +21,10 @@
 //   4. the sticky diff (Sec. 4.3): per-program transition category, the
 //      swap-out and swap-in lists in that order and the page/slot bases.
 //
-// P <= 4096 programs fit in LDS (4 keys per thread), so the whole step is one
-// launch: 5 us for tens of programs, 7 for 256, about thirty for 4096, bound by
-// the one workgroup's vector ALU and barriers; nothing here is bandwidth-bound.
+// P <= 4096 programs fit in LDS (4 per thread), so placement and diff are one
+// launch, for up to 1024 programs the whole step (5 us for tens of programs, 7
+// for 256), bound by the one workgroup's vector ALU and barriers; nothing here
+// is bandwidth-bound.
 #include "mori_internal.h"
 #include "sort.h"
 #include "wave.h"
@@ -33,14 +34,22 @@ namespace {
 
 // Four shapes, chosen by P at launch: one wave (64 threads, so every barrier
 // is a single wave's) for P <= 64, 256 threads x 1 item up to 256, 1024 x 1 up
-// to 1024 (all three sorted by merging) and
-// 1024 threads x 4 items (striped: item x = it * RT + tid) up to 4096; fewer
-// item slices mean fewer ballots per radix pass.
-constexpr int RADIX_BITS = 8;
-constexpr int RADIX = 1 << RADIX_BITS;
-constexpr int KEY_BITS = 64;
+// to 1024 and 1024 threads x 4 items (striped: item x = it * RT + tid) up to
+// 4096.  The one workgroup computes and sorts the keys of up to
+// SORT_MAX_PROGRAMS programs itself; above, and where the windows together hold
+// more than SORT_MAX_CYCLES cycles, two kernels before it do that on many
+// compute units.  Those cost about 4.5 us a plan; the one workgroup took 13 us
+// to sort 4096 programs (radix passes; merging is bound by LDS gathers and no
+// faster there) and takes 0.5 ns for each cycle it reads.  A pair of plans,
+// sorted -> counted: 4096 programs with 5 cycles each 112 -> 100 us, with 64
+// 380 -> 108; 1100 programs 92 -> 81 and 150 -> 86; 1024 programs with 5 stay
+// at 72, with 64 go from 134 to 85, 300 with 64 stay at 82.
+constexpr uint32_t SORT_MAX_PROGRAMS = 1024, SORT_MAX_CYCLES = 1u << 14;
 constexpr int ID_BITS = 12;      // a program id
 constexpr int GROUP_SHIFT = 61;  // incremental keys: listing group in the top three bits
+constexpr uint64_t ACTING_BIT = 0x80000000u;  // ... and statuses in the key, above the idleness bits
+constexpr int KEY_WG = 64, RANK_WG = 1024;
+
 // Exclusive scans of the IPT x RT items in rank order (item it of thread tid
 // has rank it * RT + tid), N values per item side by side: wave scans, the
 // per-(slice, wave) totals scanned by the first wave, and three barriers in
@@ -126,6 +135,123 @@ __device__ void claim_pages(const PlanArgs& a, uint32_t b, uint32_t nb) {
   if (err) atomicOr(a.page_err, err);
 }
 
+// A program's key and blocks (Eq. 1 or the idleness given); what is wrong with
+// its data goes to err.  Every load of the program first, none behind a branch,
+// so they are in flight together: one memory latency instead of one per load.
+__device__ inline uint64_t program_key(const PlanArgs& a, uint32_t x, uint8_t& told, uint32_t& blocks, uint32_t& err) {
+  const bool given = (a.flags & MORI_F_IDLENESS_GIVEN) != 0;
+  const bool incremental = (a.flags & MORI_F_INCREMENTAL) != 0;
+  const bool need_status = incremental || (a.flags & MORI_F_STATUS_KEY);
+  told = a.tier[x];
+  const uint32_t off0 = a.tbl_off[x], off1 = a.tbl_off[x + 1];
+  const uint8_t st = need_status ? a.status[x] : 0;
+  float rv[8], cv[8];  // the first eight cycles of the window
+  const float* w = given ? nullptr : a.window + (size_t)x * a.k * 2;
+  if (!given) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if ((uint32_t)u >= a.k) break;  // uniform
+      rv[u] = w[2 * u];
+      cv[u] = w[2 * u + 1];
+    }
+  }
+  if (told > ((a.flags & MORI_F_SSD_TIER) ? MORI_TIER_SSD : MORI_TIER_WAIT)) err |= MORI_DEV_BAD_TIER;
+  if (off1 < off0) err |= MORI_DEV_BAD_TBL_OFF;
+  blocks = off1 - off0;
+  float v;
+  if (given) {
+    v = a.idleness[x];
+    if (!(v >= 0.0f && v <= 1.0f)) err |= MORI_DEV_BAD_IDLENESS;
+  } else {
+    float t_reasoning = 0.0f, t_acting = 0.0f;
+    for (uint32_t j0 = 0; j0 < a.k; j0 += 8) {  // eight cycles' loads in flight, then the sums in order
+      if (j0 > 0) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const uint32_t j = min(j0 + u, a.k - 1);
+          rv[u] = w[2 * j];
+          cv[u] = w[2 * j + 1];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (j0 + u >= a.k) break;
+        const float r = rv[u], c = cv[u];
+        if (!(r >= 0.0f) || !(c >= 0.0f) || __builtin_isinf(r) || __builtin_isinf(c)) err |= MORI_DEV_BAD_WINDOW;
+        t_reasoning = t_reasoning + r;
+        t_acting = t_acting + c;
+      }
+    }
+    const float total = t_reasoning + t_acting;
+    if (__builtin_isinf(t_reasoning) || __builtin_isinf(t_acting) || __builtin_isinf(total)) err |= MORI_DEV_BAD_WINDOW;
+    v = (total > 0.0f) ? t_acting / total : 0.0f;
+  }
+  if (v == 0.0f) v = 0.0f;  // a negative zero keys like +0
+  const uint32_t bits = __float_as_uint(v);  // < 2^30 for idleness in [0, 1]
+  if (!incremental) {
+    uint64_t k = bits;
+    if ((a.flags & MORI_F_STATUS_KEY) && st == MORI_ST_ACTING) k |= ACTING_BIT;
+    return k;
+  }
+  if (st > MORI_ST_NEW) err |= MORI_DEV_BAD_STATUS;
+  const uint64_t acting = st == MORI_ST_ACTING;
+  uint64_t grp;
+  uint64_t sub = bits;
+  if (told == MORI_TIER_GPU || told == MORI_TIER_CPU) {
+    grp = told;  // Reasoning before Acting, then idleness: the reverse of the demotion order
+    if (acting) sub |= ACTING_BIT;
+  } else if (st == MORI_ST_NEW) {
+    grp = 3;  // new arrivals: smallest context first
+    if (blocks >= 0x80000000u) err |= MORI_DEV_BAD_TBL_OFF;
+    sub |= (uint64_t)blocks << 30;
+  } else {
+    grp = acting ? 4 : 2;
+  }
+  return (grp << GROUP_SHIFT) | sub;
+}
+
+// The table's ends.  One thread.
+__device__ inline uint32_t table_error(const PlanArgs& a) {
+  return a.tbl_off[0] != 0u || a.tbl_off[a.P] > a.tbl_len ? MORI_DEV_BAD_TBL_OFF : 0u;
+}
+
+// ---- more than one workgroup sorts well: keys and ranks by many -----------
+// Keys, one program a thread in workgroups of a wave, so that the windows are
+// read by many compute units.
+__global__ __launch_bounds__(KEY_WG) void program_keys_kernel(PlanArgs a) {
+  const uint32_t x = blockIdx.x * KEY_WG + threadIdx.x;
+  uint32_t err = 0, blocks;
+  uint8_t told;
+  if (x == 0) err |= table_error(a);
+  if (x < a.P) a.key[x] = program_key(a, x, told, blocks, err);
+  err = wave::all_or<uint32_t>(err);
+  if (threadIdx.x == 0) a.key_err[blockIdx.x] = err;
+}
+
+// Ranks, one program a wave: the programs before it are counted.  Keys of
+// rejected programs are ranked like any others (the order is total whatever
+// they hold); the placement reports the error.  What it reads of a program goes
+// to the program's rank: id | listing group << 16 | Acting bit << 20 |
+// blocks << 32.
+__global__ __launch_bounds__(RANK_WG) void program_rank_kernel(PlanArgs a) {
+  __shared__ uint64_t s_key[MORI_MAX_PROGRAMS];
+  const uint32_t chunks = (a.P + 64 * GROUP - 1) / (64 * GROUP) * GROUP;
+  const uint32_t p = blockIdx.x * (RANK_WG / 64) + (threadIdx.x >> 6);
+  const uint32_t own = min(p, a.P - 1);
+  const uint32_t off0 = a.tbl_off[own], off1 = a.tbl_off[own + 1];
+  for (uint32_t j = threadIdx.x; j < chunks * 64; j += RANK_WG) s_key[j] = j < a.P ? a.key[j] : ~0ull;
+  __syncthreads();
+  if (p >= a.P) return;
+  uint32_t rank[1];
+  uint64_t unused[1];
+  count_before<1, false>(s_key, nullptr, chunks, p, rank, unused);
+  if ((threadIdx.x & 63) == 0) {
+    const uint64_t k = s_key[p];
+    a.rank_rec[rank[0]] = p | ((k >> GROUP_SHIFT) << 16) | ((k & ACTING_BIT) ? 1ull << 20 : 0ull) |
+                          ((uint64_t)(off1 - off0) << 32);
+  }
+}
+
 // Sorts one (key, id) per thread, padded above P programs: entries 0 .. P - 1
 // (and the padding to a multiple of 64) end up ascending in s_key (and s_id
 // unless PACKED).
@@ -205,24 +331,18 @@ __device__ inline uint8_t category(uint8_t from, uint8_t to) {
   }
 }
 
-template <int RT, int IPT>
+// RANKED: program_rank_kernel has ranked the programs.
+template <int RT, int IPT, bool RANKED>
 __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   constexpr int NW = RT / 64;  // wavefronts
-  constexpr int NCNT = RADIX * NW;  // digit counters, (digit, wave)
-  constexpr int CPT = NCNT / RT;         // consecutive counters per thread in their scan
-  static_assert(NCNT % RT == 0, "whole counters per thread");
-  // counter c lives at c + c / 32: a thread's CPT consecutive counters then
-  // fall in different banks from its neighbours'
-  auto cidx = [](uint32_t c) { return c + (c >> 5); };
+  static_assert(RANKED || IPT == 1, "one program a thread is sorted");
   __shared__ uint64_t s_key[RT * IPT];  // sort scratch, then the inclusive byte prefix by rank
   __shared__ uint32_t s_id[RT * IPT];   // sort scratch, then blocks by rank
-  __shared__ uint32_t s_cnt[NCNT + NCNT / 32];
   __shared__ uint8_t s_tier[RT * IPT];
-  __shared__ uint32_t s_nblk[RT * IPT];  // blocks of program x
+  __shared__ uint32_t s_nblk[RT * IPT];  // blocks of program x, then its page base
   __shared__ uint8_t s_told[RT * IPT];   // old tier of program x
   __shared__ uint32_t s_tot[(IPT * NW + 1) * 5];
-  __shared__ uint32_t s_w32[NW + 1];
-  __shared__ unsigned long long s_or, s_and;
+  __shared__ unsigned long long s_or;
   __shared__ uint32_t s_err, s_m_gpu, s_m_cpu, s_m_ssd;
   __shared__ uint32_t s_grp[5], s_cpu_reasoning, s_k_gpu, s_k_cpu;
   __shared__ uint32_t s_n_drop, s_n_admit_cpu, s_gpu_after, s_cpu_after, s_ssd_after;
@@ -236,11 +356,9 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   const uint32_t P = a.P;
   const bool incremental = (a.flags & MORI_F_INCREMENTAL) != 0;
   const bool ssd = (a.flags & MORI_F_SSD_TIER) != 0;
-  const uint8_t top_tier = ssd ? MORI_TIER_SSD : MORI_TIER_WAIT;
   if (tid == 0) {
     s_err = 0;
     s_or = 0;
-    s_and = ~0ull;
     s_m_gpu = s_m_cpu = s_m_ssd = 0;
     for (int g = 0; g < 5; ++g) s_grp[g] = 0;
     s_cpu_reasoning = s_k_gpu = s_k_cpu = 0;
@@ -254,105 +372,31 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
   uint64_t key[IPT];
   uint32_t id[IPT];
   uint32_t err = 0;
-  if (tid == 0) {
-    if (a.tbl_off[0] != 0u) err |= MORI_DEV_BAD_TBL_OFF;
-    if (a.tbl_off[P] > a.tbl_len) err |= MORI_DEV_BAD_TBL_OFF;
-  }
-  unsigned long long k_or = 0, k_and = ~0ull;
+  uint32_t grp[IPT];    // incremental: listing group
+  bool acting[IPT];     // ... and Acting
+  uint32_t nb[IPT];
+  unsigned long long k_or = 0;
+  if constexpr (RANKED) {
+    if ((uint32_t)tid < (P + KEY_WG - 1) / KEY_WG) err = a.key_err[tid];
 #pragma unroll
-  for (int it = 0; it < IPT; ++it) {
-    const uint32_t x = it * RT + tid;
-    key[it] = ~0ull;  // padding sorts after every real key
-    id[it] = x;
-    if (x >= P) continue;
-    // every load of the program first, none behind a branch, so they are in
-    // flight together: one memory latency instead of one per load
-    const bool given = (a.flags & MORI_F_IDLENESS_GIVEN) != 0;
-    const bool need_status = incremental || (a.flags & MORI_F_STATUS_KEY);
-    const uint8_t told = a.tier[x];
-    const uint32_t off0 = a.tbl_off[x], off1 = a.tbl_off[x + 1];
-    const uint8_t st = need_status ? a.status[x] : 0;
-    float rv[8], cv[8];  // the first eight cycles of the window
-    const float* w = given ? nullptr : a.window + (size_t)x * a.k * 2;
-    if (!given) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if ((uint32_t)u >= a.k) break;  // uniform
-        rv[u] = w[2 * u];
-        cv[u] = w[2 * u + 1];
-      }
+    for (int it = 0; it < IPT; ++it) {
+      const uint32_t r = it * RT + tid;
+      const uint64_t rec = r < P ? a.rank_rec[r] : 0ull;
+      if (r < P) s_told[r] = a.tier[r];
+      id[it] = (uint32_t)rec & ((1u << ID_BITS) - 1u);
+      grp[it] = (uint32_t)(rec >> 16) & 7u;
+      acting[it] = ((rec >> 20) & 1u) != 0;
+      nb[it] = (uint32_t)(rec >> 32);
     }
-    if (told > top_tier) err |= MORI_DEV_BAD_TIER;
-    if (off1 < off0) err |= MORI_DEV_BAD_TBL_OFF;
-    s_nblk[x] = off1 - off0;
-    s_told[x] = told;
-    float v;
-    if (given) {
-      v = a.idleness[x];
-      if (!(v >= 0.0f && v <= 1.0f)) err |= MORI_DEV_BAD_IDLENESS;
-    } else {
-      float t_reasoning = 0.0f, t_acting = 0.0f;
-      for (uint32_t j0 = 0; j0 < a.k; j0 += 8) {  // eight cycles' loads in flight, then the sums in order
-        if (j0 > 0) {
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const uint32_t j = min(j0 + u, a.k - 1);
-            rv[u] = w[2 * j];
-            cv[u] = w[2 * j + 1];
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (j0 + u >= a.k) break;
-          const float r = rv[u], c = cv[u];
-          if (!(r >= 0.0f) || !(c >= 0.0f) || __builtin_isinf(r) || __builtin_isinf(c)) err |= MORI_DEV_BAD_WINDOW;
-          t_reasoning = t_reasoning + r;
-          t_acting = t_acting + c;
-        }
-      }
-      const float total = t_reasoning + t_acting;
-      if (__builtin_isinf(t_reasoning) || __builtin_isinf(t_acting) || __builtin_isinf(total))
-        err |= MORI_DEV_BAD_WINDOW;
-      v = (total > 0.0f) ? t_acting / total : 0.0f;
-    }
-    if (v == 0.0f) v = 0.0f;  // a negative zero keys like +0
-    const uint32_t bits = __float_as_uint(v);  // < 2^30 for idleness in [0, 1]
-    uint64_t k;
-    if (incremental) {
-      if (st > MORI_ST_NEW) err |= MORI_DEV_BAD_STATUS;
-      const uint64_t acting = st == MORI_ST_ACTING;
-      uint64_t grp;
-      uint64_t sub = bits;
-      if (told == MORI_TIER_GPU || told == MORI_TIER_CPU) {
-        grp = told;  // Reasoning before Acting, then idleness: the reverse of the demotion order
-        sub |= acting << 31;
-      } else if (st == MORI_ST_NEW) {
-        grp = 3;  // new arrivals: smallest context first
-        const uint32_t nb = off1 - off0;
-        if (nb >= 0x80000000u) err |= MORI_DEV_BAD_TBL_OFF;
-        sub |= (uint64_t)nb << 30;
-      } else {
-        grp = acting ? 4 : 2;
-      }
-      k = (grp << GROUP_SHIFT) | sub;
-    } else {
-      k = bits;
-      if ((a.flags & MORI_F_STATUS_KEY) && st == MORI_ST_ACTING) k |= 0x80000000u;
-    }
-    key[it] = k;
-    k_or |= k;
-    k_and &= k;
-  }
-  {
-    const uint64_t w_or = wave::all_or<uint64_t>(k_or), w_and = wave::all_and<uint64_t>(k_and);
+  } else {
+    if (tid == 0) err |= table_error(a);
+    key[0] = ~0ull;  // padding sorts after every real key
+    id[0] = tid;
+    if ((uint32_t)tid < P) k_or = key[0] = program_key(a, tid, s_told[tid], s_nblk[tid], err);
+    const uint64_t w_or = wave::all_or<uint64_t>(k_or);
     if (lane == 0 && w_or) atomicOr(&s_or, (unsigned long long)w_or);
-    if (lane == 0 && w_and != ~0ull) atomicAnd(&s_and, (unsigned long long)w_and);
   }
   if (err) atomicOr(&s_err, err);
-  if constexpr (IPT > 1) {  // the first radix pass's digit counters
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) s_cnt[cidx(j * RT + tid)] = 0;
-  }
   __syncthreads();
   if (s_err) {
     if (tid == 0) {
@@ -366,31 +410,26 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
     return;
   }
 
-  // Incremental keys: the listing group moves down from the top bits to just
-  // above the highest bit any program's priority uses (the same order), so the
-  // radix sort spends no pass on the bits between.  OR and AND of the keys
-  // follow, as the fields do not overlap.
-  uint32_t gshift = GROUP_SHIFT;
-  uint64_t kor = s_or, kand = s_and;
-  if (incremental) {
-    constexpr uint64_t SUB = (1ull << GROUP_SHIFT) - 1;
-    const uint64_t sub_or = kor & SUB;
-    gshift = sub_or ? 64u - (uint32_t)__clzll(sub_or) : 0u;
-    auto pack = [&](uint64_t k) { return ((k >> GROUP_SHIFT) << gshift) | (k & SUB); };
-#pragma unroll
-    for (int it = 0; it < IPT; ++it)
-      if (it * RT + tid < (int)P) key[it] = pack(key[it]);
-    kor = pack(kor);
-    kand = pack(kand);
-  }
-
   // ---- 2. stable sort of (key, id) ---------------------------------------
-  if constexpr (IPT == 1) {
-    // P <= 1024: one program a thread, waves sorted and lists merged in LDS.
-    // Boundary keys, and incremental ones of less than 2^20 blocks, leave room
-    // for the id in the same word.  (Counting ranks against keys in LDS took
-    // 7.1 us at 256 programs, radix passes 5.2 us at 1024 and 7.6 us with
-    // incremental keys; this 2.0 and 4.3 us.)
+  if constexpr (!RANKED) {
+    // Incremental keys: the listing group moves down from the top bits to just
+    // above the highest bit any program's priority uses (the same order), which
+    // mostly leaves room for the id.
+    uint32_t gshift = GROUP_SHIFT;
+    uint64_t kor = s_or;
+    if (incremental) {
+      constexpr uint64_t SUB = (1ull << GROUP_SHIFT) - 1;
+      const uint64_t sub_or = kor & SUB;
+      gshift = sub_or ? 64u - (uint32_t)__clzll(sub_or) : 0u;
+      auto pack = [&](uint64_t k) { return ((k >> GROUP_SHIFT) << gshift) | (k & SUB); };
+      if ((uint32_t)tid < P) key[0] = pack(key[0]);
+      kor = pack(kor);
+    }
+    // One program a thread, waves sorted and lists merged in LDS.  Boundary
+    // keys, and incremental ones of less than 2^20 blocks, leave room for the
+    // id in the same word.  (Counting ranks against keys in LDS took 7.1 us at
+    // 256 programs, radix passes 5.2 us at 1024 and 7.6 us with incremental
+    // keys; this 2.0 and 4.3 us.)
     const uint32_t x = tid;
     if ((kor >> (64 - ID_BITS)) == 0) {
       sort_programs<true>(x < P ? (key[0] << ID_BITS) | x : ~0ull, x, P, s_key, s_id);
@@ -401,101 +440,12 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
       key[0] = s_key[tid];
       id[0] = s_id[tid];
     }
-    __syncthreads();
-  } else {
-    // LSD radix sort, 8-bit digits (at most four passes over idleness keys).
-    // During the sort each wave holds a block of 64 * IPT consecutive
-    // positions (slice it of wave w: positions w * 64 * IPT + it * 64 + lane)
-    // and ranks its slices in order, a running count per (digit, wave) in LDS
-    // carrying the ranks from slice to slice; those counters, scanned in
-    // (digit, wave) order, give every group its output base, so a pass is
-    // stable.  Items move to the blocked order before the first pass and back
-    // to the striped one (item it of thread tid at it * RT + tid) in the last.
-    // Digits on which every real key agrees are skipped; padding keeps the
-    // tail.  Five barriers a pass: counts, wave totals, bases, scatter, and the
-    // read-back that also clears the next pass's counters.
-    const uint64_t varying = kor ^ kand;
-    const uint64_t lanemask_lt = (1ull << lane) - 1ull;
-    int last_shift = -1;
-    for (int shift = 0; shift < KEY_BITS; shift += RADIX_BITS)
-      if ((varying >> shift) & (RADIX - 1)) last_shift = shift;
-    const uint32_t blk = (uint32_t)wid * 64 * IPT + lane;  // this lane's position in slice 0
-    if (IPT > 1 && last_shift >= 0) {  // to the blocked order (positions are program ids here)
-#pragma unroll
-      for (int it = 0; it < IPT; ++it) {
-        s_key[it * RT + tid] = key[it];
-        s_id[it * RT + tid] = id[it];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int it = 0; it < IPT; ++it) {
-        key[it] = s_key[blk + it * 64];
-        id[it] = s_id[blk + it * 64];
-      }
-      // the first pass overwrites s_key only after its first barriers
-    }
-    for (int shift = 0; shift <= last_shift; shift += RADIX_BITS) {
-      if (((varying >> shift) & (RADIX - 1)) == 0) continue;
-      uint32_t digit[IPT], lrank[IPT];
-#pragma unroll
-      for (int it = 0; it < IPT; ++it) {
-        const uint32_t d = (uint32_t)(key[it] >> shift) & (RADIX - 1);
-        const uint64_t same = ~wave::digit_differs<RADIX_BITS>(d);
-        const uint32_t r = __popcll(same & lanemask_lt);
-        const uint32_t c = cidx(d * NW + wid);
-        const uint32_t before = s_cnt[c];  // keys of digit d in this wave's earlier slices
-        __builtin_amdgcn_wave_barrier();
-        if (r == 0) s_cnt[c] = before + __popcll(same);  // read by the next slice's lanes
-        __builtin_amdgcn_wave_barrier();
-        digit[it] = d;
-        lrank[it] = before + r;
-      }
-      __syncthreads();
-      uint32_t loc[CPT], sum = 0;
-#pragma unroll
-      for (int j = 0; j < CPT; ++j) {
-        loc[j] = s_cnt[cidx(tid * CPT + j)];
-        sum += loc[j];
-      }
-      // this thread's base: its wave's exclusive scan plus the totals of the
-      // waves before it (lane w < wid reads wave w's total)
-      const uint32_t incl = wave::incl_add(sum);
-      if (lane == 63) s_w32[wid] = incl;
-      __syncthreads();
-      uint32_t base = incl - sum + wave::sum(lane < wid ? s_w32[lane] : 0u);
-#pragma unroll
-      for (int j = 0; j < CPT; ++j) {
-        s_cnt[cidx(tid * CPT + j)] = base;
-        base += loc[j];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int it = 0; it < IPT; ++it) {
-        const uint32_t pos = s_cnt[cidx(digit[it] * NW + wid)] + lrank[it];
-        s_key[pos] = key[it];
-        s_id[pos] = id[it];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int it = 0; it < IPT; ++it) {
-        const uint32_t x = shift == last_shift ? it * RT + tid : blk + it * 64;  // striped after the last pass
-        key[it] = s_key[x];
-        id[it] = s_id[x];
-      }
-#pragma unroll
-      for (int j = 0; j < CPT; ++j) s_cnt[cidx(j * RT + tid)] = 0;  // every base of this pass is read
-      __syncthreads();
-    }
+    grp[0] = (uint32_t)(key[0] >> gshift);
+    acting[0] = gshift && (key[0] & ((1ull << gshift) - 1) & ACTING_BIT);
+    nb[0] = x < P ? s_nblk[id[0]] : 0u;
+    __syncthreads();  // s_key and s_id are reused
   }
   // item x now holds rank x: id[it] is the program at rank it * RT + tid
-  uint32_t nb[IPT];
-#pragma unroll
-  for (int it = 0; it < IPT; ++it) {
-    const uint32_t r = it * RT + tid;
-    nb[it] = 0;
-    if (r < P) nb[it] = s_nblk[id[it]];
-  }
-  __syncthreads();  // s_id is reused for blocks by rank
 #pragma unroll
   for (int it = 0; it < IPT; ++it) s_id[it * RT + tid] = nb[it];
 
@@ -519,11 +469,10 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
 #pragma unroll
     for (int it = 0; it < IPT; ++it) {
       const uint32_t r = it * RT + tid;
-      const uint32_t g = r < P ? (uint32_t)(key[it] >> gshift) : 5u;
-      const uint64_t sub = gshift ? key[it] & ((1ull << gshift) - 1) : 0ull;  // priority: Acting bit 31
+      const uint32_t g = r < P ? grp[it] : 5u;
 #pragma unroll
       for (int j = 0; j < 5; ++j) gc[j] += g == (uint32_t)j;
-      cr += g == MORI_TIER_CPU && !((sub >> 31) & 1u);
+      cr += g == MORI_TIER_CPU && !acting[it];
     }
 #pragma unroll
     for (int j = 0; j < 5; ++j) add_to(&s_grp[j], gc[j]);
@@ -828,10 +777,16 @@ hipError_t launch_rank(const PlanArgs& a, hipStream_t s) {
     const uint64_t g = ((uint64_t)a.tbl_len + 2ull * rt - 1) / (2ull * rt);
     return dim3(1 + (uint32_t)(g < 2048 ? g : 2048));
   };
-  if (a.P <= 64) hipLaunchKernelGGL((rank_partition_kernel<64, 1>), grid(64), dim3(64), 0, s, a);
-  else if (a.P <= 256) hipLaunchKernelGGL((rank_partition_kernel<256, 1>), grid(256), dim3(256), 0, s, a);
-  else if (a.P <= 1024) hipLaunchKernelGGL((rank_partition_kernel<1024, 1>), grid(1024), dim3(1024), 0, s, a);
-  else hipLaunchKernelGGL((rank_partition_kernel<1024, 4>), grid(1024), dim3(1024), 0, s, a);
+  const bool counted = a.P > SORT_MAX_PROGRAMS || (uint64_t)a.P * a.k > SORT_MAX_CYCLES;
+  if (counted) {
+    hipLaunchKernelGGL(program_keys_kernel, dim3((a.P + KEY_WG - 1) / KEY_WG), dim3(KEY_WG), 0, s, a);
+    hipLaunchKernelGGL(program_rank_kernel, dim3((a.P + RANK_WG / 64 - 1) / (RANK_WG / 64)), dim3(RANK_WG), 0, s, a);
+  }
+  if (a.P > 1024) hipLaunchKernelGGL((rank_partition_kernel<1024, 4, true>), grid(1024), dim3(1024), 0, s, a);
+  else if (counted) hipLaunchKernelGGL((rank_partition_kernel<1024, 1, true>), grid(1024), dim3(1024), 0, s, a);
+  else if (a.P <= 64) hipLaunchKernelGGL((rank_partition_kernel<64, 1, false>), grid(64), dim3(64), 0, s, a);
+  else if (a.P <= 256) hipLaunchKernelGGL((rank_partition_kernel<256, 1, false>), grid(256), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((rank_partition_kernel<1024, 1, false>), grid(1024), dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 

@@ -1,7 +1,8 @@
 // Sorting in one workgroup: waves sort 64 entries each in registers, then sorted
 // lists in LDS are merged two by two.  An entry is a (key, id) pair, or PACKED
 // one word that holds both (the id in the low bits): one compare and two
-// registers instead of three and three.  Entries are distinct.
+// registers instead of three and three.  Entries are distinct.  Or an element's
+// place is counted, by a wave that compares it with every key.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -67,6 +68,55 @@ __device__ inline uint32_t merged_place(const uint64_t* s_key, const uint32_t* s
     else hi = mid;
   }
   return min(own, sib) + (x - own) + (lo - first);
+}
+
+// For E consecutive staged elements i0 .. i0 + E - 1 of one wave (i0 a multiple
+// of E): how many staged keys come before each (lower key, or equal key and
+// lower index) and with BYTES the sum of their sizes.  The keys come in chunks
+// of 64, a multiple of GROUP of them; keys past the last element are all ones.
+// The elements' keys are uniform, so a chunk costs a 64-bit compare against a
+// scalar and an add of the carry per element.  Equal keys come first in lower
+// groups of chunks, where the compare is with key + 1, not in higher ones,
+// where it is with the key, and by index in the elements' own group.
+constexpr uint32_t GROUP = 4;  // chunks whose loads are in flight together
+template <int E, bool BYTES>
+__device__ inline void count_before(const uint64_t* s_key, const uint32_t* s_size, uint32_t chunks, uint32_t i0,
+                                    uint32_t (&rank)[E], uint64_t (&bytes)[E]) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint64_t k[E], sum[E];
+  uint32_t cnt[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    k[e] = wave::uniform(s_key[i0 + e]);
+    cnt[e] = 0;
+    sum[e] = 0;
+  }
+  auto group = [&](uint32_t c0, auto limit) {
+    uint64_t kj[GROUP];
+    uint32_t sz[GROUP];
+#pragma unroll
+    for (uint32_t g = 0; g < GROUP; ++g) {
+      kj[g] = s_key[(c0 + g) * 64 + lane];
+      sz[g] = BYTES ? s_size[(c0 + g) * 64 + lane] : 0u;
+    }
+#pragma unroll
+    for (uint32_t g = 0; g < GROUP; ++g)
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const bool before = kj[g] < limit(e, (c0 + g) * 64 + lane);
+        cnt[e] += before;
+        if (BYTES) sum[e] += before ? sz[g] : 0u;
+      }
+  };
+  const uint32_t own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(i0 / (64 * GROUP) * GROUP));
+  for (uint32_t c = 0; c < own; c += GROUP) group(c, [&](int e, uint32_t) { return k[e] + 1; });
+  group(own, [&](int e, uint32_t j) { return k[e] + (j < i0 + e); });
+  for (uint32_t c = own + GROUP; c < chunks; c += GROUP) group(c, [&](int e, uint32_t) { return k[e]; });
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    rank[e] = wave::sum(cnt[e]);
+    bytes[e] = BYTES ? wave::sum(sum[e]) : rank[e];
+  }
 }
 
 }  // namespace mori

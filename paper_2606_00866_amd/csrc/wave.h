@@ -62,6 +62,12 @@ __device__ inline uint64_t lane_of(uint64_t v, int lane) {
          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
 }
 
+// A value that every lane holds, in scalar registers.
+__device__ inline uint64_t uniform(uint64_t x) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+}
+
 // Totals over the wavefront, the same (wave-uniform) value in every lane.
 template <typename T>
 __device__ inline T sum(T v) { return lane63(incl(v, Add())); }
