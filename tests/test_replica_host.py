@@ -25,6 +25,24 @@ def test_matches_oracle(orc, seed):
         assert np.array_equal(after, orc_after)
 
 
+@pytest.mark.parametrize("P", [200, 321, 5000])
+@pytest.mark.parametrize("high", [40, 1 << 20, 1 << 40, 1 << 64])
+def test_sizes_of_any_width(orc, P, high):
+    """Sizes that differ in one to eight bytes (the radix passes), zeros of both
+    signs among the idleness, and replica counts that are no power of two."""
+    rng = np.random.default_rng([P, high % 1000003])
+    sizes = rng.integers(0, high, P, dtype=np.uint64)
+    iota = rng.choice(np.array([0.0, -0.0, 1e-40, 0.5], np.float32), P)
+    st = rng.choice(3, P, p=[0.5, 0.2, 0.3]).astype(np.uint8)
+    for R in (5, 77, 1023):
+        room = rng.integers(0, high, R, dtype=np.uint64)
+        for flags in (0, M.MORI_ADMIT_BEST_FIT):
+            rc, rep, after = M.mori_replica_admit(sizes, iota, st, room, flags)
+            orc_rc, orc_rep, orc_after = orc.replica_admit(sizes, iota, st, room, orc.ADMIT_BEST_FIT if flags else 0)
+            assert rc == M.MORI_OK and orc_rc == orc.OK
+            assert np.array_equal(rep, orc_rep) and np.array_equal(after, orc_after)
+
+
 def test_argument_checks():
     one = dict(bytes_=[1], idleness=[0.5], status=[0], room=[4])
 
