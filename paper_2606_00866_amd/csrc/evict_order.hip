@@ -16,7 +16,7 @@
 //           LDS and each wave counts, for its blocks, the blocks before it and
 //           their bytes, which are the block's place and its prefix; no
 //           workgroup waits for another.
-//   buckets (up to BUCKET_MAX) four kernels: a sorted sample gives up to 1024
+//   buckets (up to BUCKET_MAX) four or five kernels: a sorted sample gives up to 1024
 //           buckets of about equal size whatever the keys' distribution and
 //           ties; the blocks of each bucket are counted, gathered and sorted
 //           in LDS by one workgroup, which knows from the bucket totals where
