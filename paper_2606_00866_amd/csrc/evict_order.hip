@@ -16,11 +16,11 @@
 //           LDS and each wave counts, for its blocks, the blocks before it and
 //           their bytes, which are the block's place and its prefix; no
 //           workgroup waits for another.
-//   buckets (up to BUCKET_MAX) four or five kernels: a sorted sample gives up to 1024
-//           buckets of about equal size whatever the keys' distribution and
-//           ties; the blocks of each bucket are counted, gathered and sorted
-//           in LDS by one workgroup, which knows from the bucket totals where
-//           its bucket begins.
+//   buckets (up to BUCKET_MAX) four or five kernels: a sorted pseudo-random
+//           sample gives up to 1024 buckets of similar size, whatever the
+//           layout of keys and ties (evict_split.h); the blocks of each bucket
+//           are counted, gathered and sorted in LDS by one workgroup, which
+//           knows from the bucket totals where its bucket begins.
 //   radix   (above) a device-wide stable LSD radix sort:
 //     keys     build keys, validate, OR/AND of all keys;
 //     per pass (8-bit digit, 8 passes; a digit on which every key agrees needs
@@ -41,8 +41,7 @@
 //              tile totals first) and the eviction count.
 //
 // The workspace is the caller's, so nothing is allocated here.
-#include <algorithm>
-
+#include "evict_split.h"
 #include "mori_internal.h"
 #include "sort.h"
 #include "wave.h"
@@ -65,26 +64,11 @@ constexpr uint32_t FIX_SCAN_TILES = 1024;
 // (sizes given, half the blocks tied), the form before -> this one:
 //   blocks     4 096   8 192   16 384   69 938   262 144   2^20
 //   us         60->8   66->15  70->22   86->27   114->36   178->67
-// Direct counting grows with the square: 15.3 us at 8 192 blocks against 21 for
-// the buckets, about 24 at 10 240, and the keys no longer fit LDS twice as far.
 constexpr int BT = 1024, BNW = BT / 64;
-constexpr uint32_t DIRECT_MAX = 8192;
 constexpr uint32_t DIRECT_WG = 256;         // one per compute unit
-// The bucket form ends where packed entries run out of id bits and buckets of
-// the smallest count outgrow LDS.
-constexpr uint32_t BUCKET_ID_BITS = 20;
-constexpr uint32_t BUCKET_MAX = 1u << BUCKET_ID_BITS;
-constexpr uint32_t BUCKETS_MAX = 1024;
-// Eight samples a bucket, at least 1024 (more balance the buckets better, but
-// ranking them grows with the square: 4096 for 256 buckets 1.5 us slower).
-constexpr uint32_t SAMPLES_PER_BUCKET = 8, SAMPLES_MIN = 1024;
-constexpr uint32_t SAMPLES_MAX = SAMPLES_PER_BUCKET * BUCKETS_MAX;
 constexpr int SAMPLE_WG = 64;
-// Blocks per bucket aimed at while there are buckets left: 1024 is 9 us slower
-// at 131 072 blocks and 5 us at 2^19, 256 within 3 us either way.
-constexpr uint32_t BUCKET_AVG = 512;
-constexpr int BUCKET_IPT = 6;               // a bucket of up to 6144 blocks is sorted in LDS
-constexpr uint32_t BUCKET_CAP = BT * BUCKET_IPT;
+constexpr int BUCKET_IPT = BUCKET_CAP / BT;  // entries per thread that sorts a bucket
+static_assert(BUCKET_CAP % BT == 0, "whole entries per thread");
 // Blocks per thread of the partition kernels: one while that leaves a workgroup
 // for each compute unit, two above (2^20 blocks: 2 us faster than one or four).
 constexpr uint32_t PARTITION_ONE_MAX = 1u << 18;
@@ -633,14 +617,6 @@ struct BucketArgs {
   uint32_t* id;        // [N] block ids, bucket by bucket
 };
 
-// Sample j's block: a pseudo-random one of the j-th of S equal stretches of
-// block ids (so sample order is id order).
-__device__ inline uint32_t sample_block(uint32_t j, uint32_t S, uint32_t N) {
-  const uint32_t lo = (uint32_t)((uint64_t)j * N / S), hi = (uint32_t)((uint64_t)(j + 1) * N / S);
-  const uint32_t h = (j * 0x9E3779B1u) ^ ((j * 0x85EBCA77u) >> 15);
-  return lo + (uint32_t)(((uint64_t)h * (hi - lo)) >> 32);
-}
-
 __device__ inline void clear_buckets(const BucketArgs& a) {
   for (uint32_t b = threadIdx.x; b < a.B; b += BT) {
     a.count[b] = 0;
@@ -879,8 +855,9 @@ __device__ inline void sort_bucket(uint64_t (&key)[BUCKET_IPT], uint32_t (&id)[B
 // hold two types, in practice), key and id fit one word below the padding's:
 // one compare and two registers an entry instead of three and three (an entry
 // equal to the padding would share a place with it in a merge).  A bucket of more than
-// BUCKET_CAP blocks, which only a sample that misses the distribution leaves,
-// is ranked by counting, in which all workgroups share.
+// BUCKET_CAP blocks, which only times made to miss the sampled blocks leave (none
+// in sweeps of round-robin, strided and contiguous layouts), is ranked by
+// counting, in which all workgroups share.
 __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(8))) void evict_bucket_kernel(BucketArgs a) {
   __shared__ uint64_t s_key[BUCKET_CAP];
   __shared__ uint32_t s_id[BUCKET_CAP];
@@ -963,9 +940,8 @@ void launch_buckets(const EvictArgs& e, uint8_t* w, hipStream_t s) {
   const uint32_t N = e.N;
   BucketArgs a{};
   a.e = e;
-  a.B = 64;
-  while (a.B < BUCKETS_MAX && (uint64_t)a.B * BUCKET_AVG < N) a.B *= 2;
-  a.S = std::max(a.B * SAMPLES_PER_BUCKET, SAMPLES_MIN);
+  a.B = bucket_count(N);
+  a.S = sample_count(a.B);
   auto take = [&w](uint64_t bytes) {
     uint8_t* r = w;
     w += (bytes + 255) & ~255ull;

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from evict_split import largest_bucket, lib, sample_blocks
 from gpu_helpers import log
 from oracle import oracle
 from paper_2606_00866_amd import mori as M
@@ -48,13 +49,13 @@ def test_key_shapes_in_buckets(N, kind):
     check(typ, la, size, 16, 0, 16 * (N // 4))
 
 
-def sample_blocks(S, N):
-    """Block ids the bucket form samples (one in each of S stretches of ids)."""
-    j = np.arange(S, dtype=np.uint64)
-    lo, hi = j * np.uint64(N) // np.uint64(S), (j + np.uint64(1)) * np.uint64(N) // np.uint64(S)
-    m = np.uint64(0xFFFFFFFF)
-    h = ((j * np.uint64(0x9E3779B1)) & m) ^ (((j * np.uint64(0x85EBCA77)) & m) >> np.uint64(15))
-    return (lo + ((h * (hi - lo)) >> np.uint64(32))).astype(np.int64)
+@pytest.mark.parametrize("N", [300000, 1 << 20])
+def test_regular_layouts(N):
+    """Block ids dealt round-robin to 1005 programs, and strided times."""
+    i = np.arange(N, dtype=np.uint64)
+    log(f"evict layouts N={N}")
+    check(np.ones(N, np.uint8), i % np.uint64(1005), None, 16, 0, 16 * (N // 3))
+    check(np.ones(N, np.uint8), i * np.uint64(2391) & np.uint64(0xFFFFF), None, 16, 1, 16 * (N // 3))
 
 
 @pytest.mark.parametrize("var_size", [False, True])
@@ -64,7 +65,11 @@ def test_bucket_larger_than_lds(var_size):
     N = 20000
     rng = np.random.default_rng(1)
     la = rng.integers(1 << 40, (1 << 40) + 100, size=N).astype(np.uint64)
-    la[sample_blocks(1024, N)] = rng.integers(0, 1000, size=1024).astype(np.uint64)
+    sampled = sample_blocks(N)
+    la[sampled] = rng.integers(0, 1000, size=sampled.size).astype(np.uint64)
+    place = np.empty(N, np.int64)
+    place[np.argsort(la, kind="stable")] = np.arange(N)
+    assert largest_bucket(N, lambda ids: place[ids]) > lib().bucket_cap()
     size = rng.integers(1, 9, size=N).astype(np.uint32) if var_size else None
     check(np.ones(N, np.uint8), la, size, 3, 1, 3 * (N // 2))
 
