@@ -355,7 +355,10 @@ int mori_evict_workspace(uint32_t num_blocks, uint64_t* bytes);
  * `stream`: order[j] (device [N]) = block evicted j-th; prefix[j] (device [N],
  * may be NULL) = bytes freed by the first j+1 evictions; result (device [2]) =
  * {fewest evictions that free at least need_bytes (N if all of them free
- * less, 0 when need_bytes is 0), MORI_DEV_* error bits}.  workspace: device
+ * less, 0 when need_bytes is 0), MORI_DEV_* error bits}.  The time depends
+ * little on how types and times lie over the block ids; only times made to miss
+ * the blocks the call samples make it long (2^20 blocks: up to 9 ms).
+ * workspace: device
  * memory of at least mori_evict_workspace bytes, 256-B aligned, owned by the
  * caller and used only while the call's work runs.  Nothing is allocated.
  * EINVAL: null pointers, misaligned or short workspace, bad tier. */

@@ -850,64 +850,176 @@ __device__ inline void sort_bucket(uint64_t (&key)[BUCKET_IPT], uint32_t (&id)[B
   }
 }
 
+// The least (key, id) with rank[e] of the n entries below it, for two ranks at
+// once, in k[e] and i[e]: byte by byte from the top, the byte's value is the one
+// that holds the rank among the entries that agree with the bytes found.  A rank
+// that reaches zero is done (the bytes left are zero).  Every thread calls it.
+__device__ inline void select_ranks(const uint64_t* key, const uint32_t* id, uint32_t n, uint32_t (&rank)[2],
+                                    uint64_t (&k)[2], uint32_t (&i)[2], uint32_t (*s_cnt)[256], uint32_t* s_w) {
+  __shared__ uint32_t s_byte[2], s_before[2];
+  constexpr int ID_BYTES = (BUCKET_ID_BITS + 7) / 8;
+  constexpr int U = 2;  // entries per thread whose loads are in flight together
+  const uint32_t tid = threadIdx.x;
+  const uint64_t lanemask_lt = (1ull << (tid & 63)) - 1ull;
+  for (int byte = 8 + ID_BYTES - 1; byte >= 0 && (rank[0] | rank[1]); --byte) {
+    const bool in_key = byte >= ID_BYTES;
+    const int shift = 8 * (in_key ? byte - ID_BYTES : byte);
+    if (tid < 256) s_cnt[0][tid] = s_cnt[1][tid] = 0;
+    __syncthreads();
+    for (uint32_t x0 = 0; x0 < n; x0 += U * BT) {  // uniform: the ballots need every lane
+      uint64_t kx[U];
+      uint32_t ix[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t x = min(x0 + u * BT + tid, n - 1);
+        kx[u] = key[x];
+        ix[u] = in_key ? 0u : id[x];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool valid = x0 + u * BT + tid < n;
+        const uint32_t d = (in_key ? (uint32_t)(kx[u] >> shift) : ix[u] >> shift) & 255u;
+        const uint64_t same = ~wave::digit_differs<8>(d);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const bool agrees = valid && (in_key ? (kx[u] ^ k[e]) >> shift >> 8 == 0
+                                               : kx[u] == k[e] && (ix[u] ^ i[e]) >> shift >> 8 == 0);
+          const uint64_t group = same & __ballot(agrees);
+          if (agrees && (group & lanemask_lt) == 0) atomicAdd(&s_cnt[e][d], (uint32_t)__popcll(group));
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const uint32_t c = tid < 256 ? s_cnt[e][tid] : 0u;
+      uint32_t total;
+      const uint32_t before = scan_wg(c, s_w, &total);
+      if (before <= rank[e] && rank[e] - before < c) {
+        s_byte[e] = tid;
+        s_before[e] = before;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      if (rank[e]) {
+        rank[e] -= s_before[e];
+        if (in_key) k[e] |= (uint64_t)s_byte[e] << shift;
+        else i[e] |= s_byte[e] << shift;
+      }
+    __syncthreads();  // s_byte and s_before are reused
+  }
+}
+
+// The entries of BUCKET_CAP ranks from r on (or those there are) of a bucket of
+// `all` blocks that begins at `first`, in any order, to s_key and s_id; returns
+// their number.  *below: size units of the bucket's entries before them, *least:
+// no key of theirs is below it.  Every thread calls it.
+__device__ inline uint32_t gather_piece(const BucketArgs& a, uint32_t first, uint32_t all, uint32_t r,
+                                        uint64_t* below, uint64_t* least, uint64_t* s_key, uint32_t* s_id,
+                                        uint64_t* s_w64) {
+  __shared__ uint32_t s_cnt[2][256];
+  __shared__ uint32_t s_w[BNW];
+  __shared__ uint32_t s_taken;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t n = min(all - r, BUCKET_CAP);
+  const bool last = r + n == all;
+  uint32_t rank[2] = {r, last ? 0u : r + n};
+  uint64_t k[2] = {0, last ? ~0ull : 0ull};
+  uint32_t i[2] = {0, last ? ~0u : 0u};
+  select_ranks(a.key + first, a.id + first, all, rank, k, i, s_cnt, s_w);
+  if (tid == 0) s_taken = 0;
+  __syncthreads();
+  uint64_t lower = 0;
+#pragma unroll 1
+  for (uint32_t x = tid; x < all; x += BT) {
+    const uint64_t kx = a.key[first + x];
+    const uint32_t ix = a.id[first + x];
+    if (pair_less(kx, ix, k[0], i[0])) {
+      lower += a.e.size ? a.e.size[ix] : 1u;
+    } else if (pair_less(kx, ix, k[1], i[1])) {
+      const uint32_t at = atomicAdd(&s_taken, 1u);  // below n: those entries are n
+      s_key[at] = kx;
+      s_id[at] = ix;
+    }
+  }
+  scan_wg(lower, s_w64, below);
+  __syncthreads();
+  *least = k[0];
+  return n;
+}
+
 // One bucket per workgroup, sorted in LDS and written out with the prefix.
 // Where the bucket's keys span less than 2^44 - 1 (all but the few buckets that
 // hold two types, in practice), key and id fit one word below the padding's:
 // one compare and two registers an entry instead of three and three (an entry
-// equal to the padding would share a place with it in a merge).  A bucket of more than
-// BUCKET_CAP blocks, which only times made to miss the sampled blocks leave (none
-// in sweeps of round-robin, strided and contiguous layouts), is ranked by
-// counting, in which all workgroups share.
+// equal to the padding would share a place with it in a merge).
+//
+// A bucket of more than BUCKET_CAP blocks, which only times made to miss the
+// sampled blocks leave (none in sweeps of round-robin, strided and contiguous
+// layouts), is left to the workgroups past the buckets': each takes BUCKET_CAP
+// of its ranks, finds their ends by selection (at most 11 passes over the
+// bucket) and sorts the entries between.  With all but the sample in one bucket
+// a call takes 0.19-0.28 ms at 20 000 blocks (times distinct - tied), 1.8-2.5 at
+// 300 000, 6.1-8.7 at 2^20; ranking every entry against all the others, as
+// before, grew with the square.  The idle workgroups cost 0.5 us at 2^20 blocks.
 __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(8))) void evict_bucket_kernel(BucketArgs a) {
   __shared__ uint64_t s_key[BUCKET_CAP];
   __shared__ uint32_t s_id[BUCKET_CAP];
   __shared__ uint64_t s_w64[BNW];
   __shared__ uint32_t s_wide;
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint32_t tid = threadIdx.x;
   const uint64_t unit = a.e.unit_bytes;
   const uint64_t err = *a.err;
-  const uint32_t first = a.first[blockIdx.x], n = a.first[blockIdx.x + 1] - first;
-  uint64_t below = a.below[blockIdx.x];
-  const uint64_t least = blockIdx.x ? a.spl_key[blockIdx.x - 1] : 0ull;  // no key of the bucket is below it
   if (blockIdx.x == 0 && tid == 0) finish_result(a.e, err, a.below[a.B] * unit);
   if (err) return;
   if (tid == 0) s_wide = 0;
-  if (*a.over)
-    for (uint32_t b = 0; b < a.B; ++b) {
-      const uint32_t first = a.first[b], n = a.first[b + 1] - first;
-      const uint64_t below = a.below[b];
-      if (n > BUCKET_CAP)
-        for (uint32_t x = blockIdx.x * BNW + wid; x < n; x += gridDim.x * BNW) {
-          const uint64_t k = a.key[first + x];
-          const uint32_t id = a.id[first + x];
-          uint32_t rank = 0;
-          uint64_t before = 0;
-          for (uint32_t j = lane; j < n; j += 64) {
-            const uint32_t ij = a.id[first + j];
-            if (pair_less(a.key[first + j], ij, k, id)) {
-              ++rank;
-              before += a.e.size ? a.e.size[ij] : 1u;
-            }
-          }
-          rank = wave::sum(rank);
-          before = wave::sum(before);
-          const uint64_t own = a.e.size ? a.e.size[id] : 1u;
-          if (lane == 0) emit(a.e, first + rank, id, (below + before + own) * unit, own * unit);
-        }
-    }
-  if (n == 0 || n > BUCKET_CAP) return;
-  const uint32_t m = (n + 63) & ~63u;
+  uint32_t first, n;
+  uint64_t below, least;  // no key is below `least`
   uint64_t key[BUCKET_IPT];
   uint32_t id[BUCKET_IPT];
+  if (blockIdx.x < a.B) {
+    first = a.first[blockIdx.x];
+    n = a.first[blockIdx.x + 1] - first;
+    below = a.below[blockIdx.x];
+    least = blockIdx.x ? a.spl_key[blockIdx.x - 1] : 0ull;
+    if (n == 0 || n > BUCKET_CAP) return;
+#pragma unroll
+    for (int it = 0; it < BUCKET_IPT; ++it) {
+      const uint32_t x = it * BT + tid;
+      if (it * BT >= n) break;  // uniform
+      key[it] = x < n ? a.key[first + x] : ~0ull;
+      id[it] = x < n ? a.id[first + x] : ~0u;
+    }
+  } else {
+    if (!*a.over) return;
+    uint32_t b = 0, r = 0, piece = a.B;  // piece: the workgroup of ranks r.. of bucket b
+    for (; b < a.B; ++b) {
+      const uint32_t all = a.first[b + 1] - a.first[b];
+      if (all <= BUCKET_CAP) continue;
+      r = (blockIdx.x - piece) * BUCKET_CAP;
+      if (r < all) break;
+      piece += (all + BUCKET_CAP - 1) / BUCKET_CAP;
+    }
+    if (b == a.B) return;
+    first = a.first[b];
+    n = gather_piece(a, first, a.first[b + 1] - first, r, &below, &least, s_key, s_id, s_w64);
+    first += r;
+    below += a.below[b];
+#pragma unroll
+    for (int it = 0; it < BUCKET_IPT; ++it) {
+      const uint32_t x = it * BT + tid;
+      if (it * BT >= n) break;  // uniform
+      key[it] = x < n ? s_key[x] : ~0ull;
+      id[it] = x < n ? s_id[x] : ~0u;
+    }
+  }
+  const uint32_t m = (n + 63) & ~63u;
   bool wide = false;
 #pragma unroll
-  for (int it = 0; it < BUCKET_IPT; ++it) {
-    const uint32_t x = it * BT + tid;
-    if (x >= m) break;
-    key[it] = x < n ? a.key[first + x] : ~0ull;
-    id[it] = x < n ? a.id[first + x] : ~0u;
-    wide |= x < n && ((key[it] - least + 1) >> (64 - BUCKET_ID_BITS)) != 0;
-  }
+  for (int it = 0; it < BUCKET_IPT; ++it)
+    wide |= it * BT + tid < n && ((key[it] - least + 1) >> (64 - BUCKET_ID_BITS)) != 0;
   __syncthreads();  // s_wide is zero
   if (wide) s_wide = 1;
   __syncthreads();
@@ -974,7 +1086,8 @@ void launch_buckets(const EvictArgs& e, uint8_t* w, hipStream_t s) {
     hipLaunchKernelGGL((evict_partition_kernel<2, true>), grid, dim3(BT), 0, s, a);
     hipLaunchKernelGGL((evict_partition_kernel<2, false>), grid, dim3(BT), 0, s, a);
   }
-  hipLaunchKernelGGL(evict_bucket_kernel, dim3(a.B), dim3(BT), 0, s, a);
+  // a bucket of n > BUCKET_CAP blocks has at most 2 n / BUCKET_CAP pieces
+  hipLaunchKernelGGL(evict_bucket_kernel, dim3(a.B + N / (BUCKET_CAP / 2)), dim3(BT), 0, s, a);
 }
 
 void launch_radix(EvictArgs& a, uint8_t* w, hipStream_t s) {

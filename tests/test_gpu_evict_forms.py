@@ -74,6 +74,39 @@ def test_bucket_larger_than_lds(var_size):
     check(np.ones(N, np.uint8), la, size, 3, 1, 3 * (N // 2))
 
 
+@pytest.mark.parametrize("kind", ["first", "middle", "two", "ties", "wide"])
+@pytest.mark.parametrize("N", [15000, 33000, 300000, 1 << 20])
+def test_buckets_cut_into_pieces(N, kind):
+    """Blocks that no sample meets lie in one bucket (before all sampled blocks,
+    amid them, or in two stretches between them), with times of their own, a few
+    tied times (the pieces end between ids) or keys over all types and times."""
+    rng = np.random.default_rng(N)
+    sampled = sample_blocks(N)
+    typ = np.ones(N, np.uint8)
+    base = np.uint64(1 << 41)
+    la = base + rng.integers(0, 8 if kind == "ties" else 1 << 40, size=N).astype(np.uint64)
+    outer = rng.integers(0, 1 << 40, size=sampled.size).astype(np.uint64)
+    above = np.arange(sampled.size) % 2 == 1
+    if kind == "first":
+        above[:] = True
+    la[sampled] = outer + np.where(above, np.uint64(1 << 43), np.uint64(0))
+    if kind == "two":
+        la[np.arange(N) % 2 == 1] += np.uint64(1 << 42)
+        third = np.arange(sampled.size) % 3
+        la[sampled] = outer + np.array([0, (1 << 41) + (1 << 40), 1 << 43], np.uint64)[third]
+    if kind == "wide":
+        typ = rng.integers(0, 3, size=N).astype(np.uint8)
+        la = rng.integers(1 << 20, 1 << 62, size=N).astype(np.uint64)
+        typ[sampled] = np.where(above, 0, 2)
+        la[sampled] = np.where(above, np.uint64((1 << 62) - 1), np.uint64(0))
+    place = np.empty(N, np.int64)
+    place[np.lexsort((la, 2 - typ.astype(np.int64)))] = np.arange(N)
+    assert largest_bucket(N, lambda ids: place[ids]) > lib().bucket_cap()
+    size = rng.integers(0, 9, size=N).astype(np.uint32)
+    log(f"evict {kind} pieces N={N}")
+    check(typ, la, size, 3, 0, 3 * (int(size.sum()) // 2))
+
+
 @pytest.mark.parametrize("span", [(1 << 44) - 2, (1 << 44) - 1, 1 << 44])
 def test_packing_limit(span):
     """The last of 2^20 blocks, all others of one time, is `span` newer: at
