@@ -371,7 +371,7 @@ int mori_evict_order(const mori_blocks* blocks, uint32_t tier, uint64_t need_byt
  * workspace in a device array the library holds on each GPU for the life of
  * the process, instead of a caller buffer.  Same result for the same input;
  * at most MORI_EVICT_NOALLOC_MAX_BLOCKS blocks (ENOSPC above; the array is
- * about 17.5 MiB per GPU).  Nothing is allocated: the array's device address
+ * about 6.1 MiB per GPU).  Nothing is allocated: the array's device address
  * is looked up on the first call on each GPU (call it once before a capture
  * starts), and each call enqueues kernels only, which clear what must start
  * at zero.  Every call on one GPU uses the same array: calls whose work

@@ -9,12 +9,16 @@
 // the array's name to a kernel or a copy: only that looked-up address.
 #include <mutex>
 
+#include "evict_split.h"
 #include "mori_internal.h"
 
 namespace mori {
 namespace {
 
-constexpr uint64_t kScratchBytes = evict_workspace_bytes(MORI_EVICT_NOALLOC_MAX_BLOCKS);
+// The form is chosen by the number of blocks alone, so calls here use the bucket
+// form's pieces at most, which grow with the blocks.
+static_assert(MORI_EVICT_NOALLOC_MAX_BLOCKS <= BUCKET_MAX, "no radix passes");
+constexpr uint64_t kScratchBytes = bucket_layout(MORI_EVICT_NOALLOC_MAX_BLOCKS).bytes;
 static_assert(kScratchBytes % 256 == 0, "workspace pieces are 256-B aligned");
 
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
@@ -48,7 +52,6 @@ extern "C" int mori_evict_order_noalloc(const mori_blocks* b, uint32_t tier, uin
   if (tier != MORI_TIER_GPU && tier != MORI_TIER_CPU) return MORI_EINVAL;
   if (b->num_blocks && (!b->type || !b->last_access || !order)) return MORI_EINVAL;
   if (b->num_blocks > MORI_EVICT_NOALLOC_MAX_BLOCKS) return MORI_ENOSPC;
-  if (evict_workspace_bytes(b->num_blocks) > kScratchBytes) return MORI_ENOSPC;  // not reached: see above
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
     (void)hipGetLastError();

@@ -1054,23 +1054,19 @@ void launch_buckets(const EvictArgs& e, uint8_t* w, hipStream_t s) {
   a.e = e;
   a.B = bucket_count(N);
   a.S = sample_count(a.B);
-  auto take = [&w](uint64_t bytes) {
-    uint8_t* r = w;
-    w += (bytes + 255) & ~255ull;
-    return r;
-  };
-  a.key = reinterpret_cast<uint64_t*>(take(8ull * N));
-  a.id = reinterpret_cast<uint32_t*>(take(4ull * N));
-  a.spl_key = reinterpret_cast<uint64_t*>(take(8 * BUCKETS_MAX));
-  a.units = reinterpret_cast<uint64_t*>(take(8 * BUCKETS_MAX));
-  a.spl_id = reinterpret_cast<uint32_t*>(take(4 * BUCKETS_MAX));
-  a.count = reinterpret_cast<uint32_t*>(take(4 * BUCKETS_MAX));
-  a.taken = reinterpret_cast<uint32_t*>(take(4 * BUCKETS_MAX));
-  a.first = reinterpret_cast<uint32_t*>(take(4 * (BUCKETS_MAX + 1)));
-  a.below = reinterpret_cast<uint64_t*>(take(8 * (BUCKETS_MAX + 1)));
-  a.over = reinterpret_cast<uint32_t*>(take(4));
-  a.sample = reinterpret_cast<uint64_t*>(take(8 * SAMPLES_MAX));
-  a.err = reinterpret_cast<uint64_t*>(take(8));
+  const BucketLayout l = bucket_layout(N);
+  a.key = reinterpret_cast<uint64_t*>(w + l.key);
+  a.id = reinterpret_cast<uint32_t*>(w + l.id);
+  a.spl_key = reinterpret_cast<uint64_t*>(w + l.spl_key);
+  a.units = reinterpret_cast<uint64_t*>(w + l.units);
+  a.spl_id = reinterpret_cast<uint32_t*>(w + l.spl_id);
+  a.count = reinterpret_cast<uint32_t*>(w + l.count);
+  a.taken = reinterpret_cast<uint32_t*>(w + l.taken);
+  a.first = reinterpret_cast<uint32_t*>(w + l.first);
+  a.below = reinterpret_cast<uint64_t*>(w + l.below);
+  a.over = reinterpret_cast<uint32_t*>(w + l.over);
+  a.sample = reinterpret_cast<uint64_t*>(w + l.sample);
+  a.err = reinterpret_cast<uint64_t*>(w + l.err);
   if (a.S <= DIRECT_WG * BNW) {
     hipLaunchKernelGGL((evict_splitter_kernel<1, false>), dim3(DIRECT_WG), dim3(BT), 0, s, a);
   } else {
@@ -1091,27 +1087,17 @@ void launch_buckets(const EvictArgs& e, uint8_t* w, hipStream_t s) {
 }
 
 void launch_radix(EvictArgs& a, uint8_t* w, hipStream_t s) {
-  const uint64_t tile = (uint64_t)ET * EIPT;
-  const uint64_t N = a.N;
-  a.ntiles = (uint32_t)((N + tile - 1) / tile);
-  auto up = [](uint64_t b) { return (b + 255) & ~255ull; };
-  a.keys[0] = reinterpret_cast<uint64_t*>(w);
-  w += up(8ull * N);
-  a.keys[1] = reinterpret_cast<uint64_t*>(w);
-  w += up(8ull * N);
-  a.vals[0] = reinterpret_cast<uint32_t*>(w);
-  w += up(4ull * N);
-  a.vals[1] = reinterpret_cast<uint32_t*>(w);
-  w += up(4ull * N);
-  a.hist = reinterpret_cast<uint32_t*>(w);
-  w += up(4ull * 256 * a.ntiles);
-  a.dtot = reinterpret_cast<uint32_t*>(w);
-  w += up(4 * 256);
-  a.tile_sum = reinterpret_cast<uint64_t*>(w);
-  w += up(8ull * a.ntiles);
-  if (!a.prefix) a.prefix = reinterpret_cast<uint64_t*>(w);
-  w += up(8ull * N);
-  a.misc = reinterpret_cast<uint64_t*>(w);
+  const RadixLayout l = radix_layout(a.N);
+  a.ntiles = radix_tiles(a.N);
+  for (int i = 0; i < 2; ++i) {
+    a.keys[i] = reinterpret_cast<uint64_t*>(w + l.keys[i]);
+    a.vals[i] = reinterpret_cast<uint32_t*>(w + l.vals[i]);
+  }
+  a.hist = reinterpret_cast<uint32_t*>(w + l.hist);
+  a.dtot = reinterpret_cast<uint32_t*>(w + l.dtot);
+  a.tile_sum = reinterpret_cast<uint64_t*>(w + l.tile_sum);
+  if (!a.prefix) a.prefix = reinterpret_cast<uint64_t*>(w + l.prefix);
+  a.misc = reinterpret_cast<uint64_t*>(w + l.misc);
   hipLaunchKernelGGL(evict_init_kernel, dim3(1), dim3(1), 0, s, a);
   hipLaunchKernelGGL(evict_keys_kernel, dim3(a.ntiles < KEY_WG_MAX ? a.ntiles : KEY_WG_MAX), dim3(ET), 0, s, a);
   for (int shift = 0; shift < 64; shift += 8) {

@@ -1,5 +1,5 @@
-// How the eviction order chooses its form and splits blocks into buckets: plain
-// arithmetic, for the kernels and for host code alike.
+// How the eviction order chooses its form, lays out its workspace and splits
+// blocks into buckets: plain arithmetic, for the kernels and for host code alike.
 #pragma once
 #include <stdint.h>
 
@@ -50,5 +50,74 @@ constexpr uint32_t sample_block(uint32_t j, uint32_t S, uint32_t N) {
   const uint32_t lo = (uint32_t)((uint64_t)j * N / S), hi = (uint32_t)((uint64_t)(j + 1) * N / S);
   return lo + (uint32_t)(((uint64_t)mix(j) * (hi - lo)) >> 32);
 }
+
+// A form's pieces of the workspace, as byte offsets in it; `bytes` is where the
+// last one ends.  Pieces are 256-B aligned.
+class Pieces {
+ public:
+  constexpr uint64_t take(uint64_t bytes) {
+    const uint64_t at = end_;
+    end_ += (bytes + 255) & ~255ull;
+    return at;
+  }
+  constexpr uint64_t end() const { return end_; }
+
+ private:
+  uint64_t end_ = 0;
+};
+
+struct BucketLayout {
+  uint64_t key, id, spl_key, units, spl_id, count, taken, first, below, over, sample, err, bytes;
+};
+constexpr BucketLayout bucket_layout(uint32_t N) {
+  Pieces p;
+  BucketLayout l{};
+  l.key = p.take(8ull * N);
+  l.id = p.take(4ull * N);
+  l.spl_key = p.take(8 * BUCKETS_MAX);
+  l.units = p.take(8 * BUCKETS_MAX);
+  l.spl_id = p.take(4 * BUCKETS_MAX);
+  l.count = p.take(4 * BUCKETS_MAX);
+  l.taken = p.take(4 * BUCKETS_MAX);
+  l.first = p.take(4 * (BUCKETS_MAX + 1));
+  l.below = p.take(8 * (BUCKETS_MAX + 1));
+  l.over = p.take(4);
+  l.sample = p.take(8 * SAMPLES_MAX);
+  l.err = p.take(8);
+  l.bytes = p.end();
+  return l;
+}
+
+// Radix tiles: workgroup size and keys per thread.
+constexpr int EVICT_WG = 256;
+constexpr int EVICT_KEYS_PER_THREAD = 8;
+constexpr uint32_t radix_tiles(uint32_t N) {
+  constexpr uint64_t tile = (uint64_t)EVICT_WG * EVICT_KEYS_PER_THREAD;
+  return (uint32_t)(((uint64_t)N + tile - 1) / tile);
+}
+struct RadixLayout {
+  uint64_t keys[2], vals[2], hist, dtot, tile_sum, prefix, misc, bytes;
+};
+constexpr RadixLayout radix_layout(uint32_t N) {
+  const uint32_t ntiles = radix_tiles(N);
+  Pieces p;
+  RadixLayout l{};
+  l.keys[0] = p.take(8ull * N);
+  l.keys[1] = p.take(8ull * N);
+  l.vals[0] = p.take(4ull * N);
+  l.vals[1] = p.take(4ull * N);
+  l.hist = p.take(4ull * 256 * ntiles);
+  l.dtot = p.take(4 * 256);
+  l.tile_sum = p.take(8ull * ntiles);
+  l.prefix = p.take(8ull * N);
+  l.misc = p.take(8 * 4);
+  l.bytes = p.end();
+  return l;
+}
+
+// What mori_evict_order asks of its caller: one formula for all N, above every
+// form's need (direct counting uses no workspace, the buckets 12 B a block and
+// under 150 KB, the radix passes about 32.5 B a block).
+constexpr uint64_t evict_workspace_bytes(uint32_t N) { return radix_layout(N).bytes + (1u << 20); }
 
 }  // namespace mori

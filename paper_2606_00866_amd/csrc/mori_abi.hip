@@ -27,6 +27,7 @@
 #include <new>
 #include <vector>
 
+#include "evict_split.h"
 #include "mori_internal.h"
 
 using namespace mori;

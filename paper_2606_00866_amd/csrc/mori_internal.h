@@ -133,22 +133,6 @@ struct TranslateArgs {
   uint32_t* swap_err;       // [2]: this direction's word is swap_err[dir_in]
 };
 
-// Typed eviction order: workgroup size and keys per thread of a radix tile.
-constexpr int EVICT_WG = 256;
-constexpr int EVICT_KEYS_PER_THREAD = 8;
-
-// Device workspace of the eviction order for N blocks, in the order the radix
-// form lays it out (each piece 256-B aligned): two key and two value buffers,
-// the tile histogram, digit totals, tile sums, a prefix buffer and a few words
-// of results.  The bucket form takes less than half of it.
-constexpr uint64_t evict_workspace_bytes(uint32_t N) {
-  const uint64_t tile = (uint64_t)EVICT_WG * EVICT_KEYS_PER_THREAD;
-  const uint64_t ntiles = ((uint64_t)N + tile - 1) / tile;
-  auto up = [](uint64_t b) { return (b + 255) & ~255ull; };
-  return 2 * up(8ull * N) + 2 * up(4ull * N) + up(4ull * 256 * ntiles) + up(4 * 256) + up(8ull * ntiles) +
-         up(8ull * N) + up(8 * 4) + (1u << 20);
-}
-
 // launchers (return the launch error)
 hipError_t launch_rank(const PlanArgs& a, hipStream_t s);
 hipError_t launch_clear_owner(const PlanArgs& a, hipStream_t s);

@@ -18,6 +18,9 @@ extern "C" uint32_t bucket_max() { return BUCKET_MAX; }
 extern "C" uint32_t bucket_cap() { return BUCKET_CAP; }
 extern "C" uint32_t buckets(uint32_t N) { return bucket_count(N); }
 extern "C" uint32_t samples(uint32_t N) { return sample_count(bucket_count(N)); }
+extern "C" uint64_t bucket_bytes(uint32_t N) { return bucket_layout(N).bytes; }
+extern "C" uint64_t radix_bytes(uint32_t N) { return radix_layout(N).bytes; }
+extern "C" uint64_t workspace_bytes(uint32_t N) { return evict_workspace_bytes(N); }
 extern "C" void sampled(uint32_t N, int64_t* ids) {
   for (uint32_t j = 0, S = samples(N); j < S; ++j) ids[j] = sample_block(j, S, N);
 }
@@ -31,7 +34,10 @@ def lib():
         with open(src, "w") as f:
             f.write(SOURCE)
         subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", CSRC, src, "-o", so], check=True)
-        return ctypes.CDLL(so)
+        L = ctypes.CDLL(so)
+    for f in (L.bucket_bytes, L.radix_bytes, L.workspace_bytes):
+        f.argtypes, f.restype = [ctypes.c_uint32], ctypes.c_uint64
+    return L
 
 
 @functools.lru_cache(None)
@@ -42,9 +48,13 @@ def sample_blocks(N):
     return ids
 
 
-def largest_bucket(N, place):
-    """Blocks in the largest bucket; place(ids): the place of each block in the
-    order by (key, id)."""
+def bucket_starts(N, place):
+    """Where each bucket begins in the order by (key, id), and N; place(ids):
+    each block's place in that order."""
     B, at = lib().buckets(N), np.sort(place(sample_blocks(N)))
-    splitters = at[:: at.size // B][1:]
-    return int(np.diff(np.concatenate([[0], splitters, [N]])).max())
+    return np.concatenate([[0], at[:: at.size // B][1:], [N]])
+
+
+def largest_bucket(N, place):
+    """Blocks in the largest bucket."""
+    return int(np.diff(bucket_starts(N, place)).max())

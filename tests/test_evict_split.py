@@ -63,3 +63,16 @@ def test_contiguous_runs(N):
 
         worst = max(worst, largest_bucket(N, place))
     assert worst <= lib().bucket_cap(), worst
+
+
+def test_workspace_holds_every_form():
+    """What the caller is asked for covers the form each size takes, and the
+    bucket form's need never falls with more blocks (a fixed array sized for the
+    most blocks holds any fewer)."""
+    L = lib()
+    sizes = [L.direct_max() + 1, 8500, 16384, 32768, 32769, 69938, 1 << 18, (1 << 18) + 1, 1 << 19, (1 << 20) - 1, 1 << 20]
+    need = [L.bucket_bytes(N) for N in sizes]
+    assert need == sorted(need)
+    assert all(L.workspace_bytes(N) >= n for N, n in zip(sizes, need))
+    for N in (L.bucket_max() + 1, (1 << 21) + 5000, (1 << 32) - 1):
+        assert L.workspace_bytes(N) >= L.radix_bytes(N) >= 32 * N
