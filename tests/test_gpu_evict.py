@@ -1,9 +1,12 @@
-"""GPU parity of the typed eviction order (Sec. 4.3.2): libmori's device radix
-sort and reclaim prefix against the oracle, element by element."""
+"""GPU parity of the typed eviction order (Sec. 4.3.2): libmori's order and
+reclaim prefix against the oracle, element by element, in each of its forms
+(direct counting up to 8192 blocks, sorted buckets up to 2^20, radix passes in
+tiles of 2048 keys above; past 1024 tiles the prefix has kernels of its own)."""
 import numpy as np
 import pytest
 import torch
 
+from evict_split import bucket_starts, lib
 from gpu_helpers import log
 from oracle import oracle
 from paper_2606_00866_amd import mori as M
@@ -57,9 +60,12 @@ def test_random_small(seed):
     check(typ, la, size, 3, tier, need)
 
 
-def test_degenerate_keys():
+RADIX = [(1 << 20) + 5000, (1 << 21) + 5000]  # the prefix finished by one kernel, by three
+
+
+@pytest.mark.parametrize("N", [1000, 10000, *RADIX])
+def test_degenerate_keys(N):
     """All keys equal (every radix pass is skipped) and a single varying digit."""
-    N = 10000
     check(np.zeros(N, np.uint8), np.full(N, 7, np.uint64), None, 1, 0, 5000)
     la = np.zeros(N, np.uint64)
     la[::3] = 255
@@ -67,7 +73,7 @@ def test_degenerate_keys():
     check(np.full(N, 2, np.uint8), np.full(N, (1 << 62) - 1, np.uint64), None, 1, 0, N + 5)
 
 
-@pytest.mark.parametrize("N", [69938, 131072, 300000, 1 << 20])  # look-back passes up to 131072, three kernels above
+@pytest.mark.parametrize("N", [69938, 131072, 300000, 1 << 20])
 def test_large(N):
     rng = np.random.default_rng(N)
     typ, la, size = eviction_blocks(rng, N, programs=1024, tie_frac=0.5)
@@ -76,15 +82,18 @@ def test_large(N):
         check(typ, la, size, 2 << 20, tier, (N // 3) * (2 << 20))
 
 
-def test_bad_blocks_reported():
-    typ = np.zeros(100, np.uint8)
+@pytest.mark.parametrize("N", [100, 70000, *RADIX])
+def test_bad_blocks_reported(N):
+    typ = np.zeros(N, np.uint8)
     typ[40] = 3
-    _, _, res = run_gpu(typ, np.zeros(100, np.uint64), None, 1, 0, 10)
-    assert res[1] & M.MORI_DEV_BAD_BLOCK and res[0] == 0
-    la = np.zeros(100, np.uint64)
-    la[7] = 1 << 62
-    _, _, res = run_gpu(np.zeros(100, np.uint8), la, None, 1, 1, 10)
-    assert res[1] & M.MORI_DEV_BAD_BLOCK
+    _, _, res = run_gpu(typ, np.zeros(N, np.uint64), None, 1, 0, 10)
+    assert list(res) == [0, M.MORI_DEV_BAD_BLOCK]
+    la = np.zeros(N, np.uint64)
+    for at in (7, N - 1):
+        la[at] = 1 << 62
+        _, _, res = run_gpu(np.zeros(N, np.uint8), la, None, 1, 1, 10)
+        assert list(res) == [0, M.MORI_DEV_BAD_BLOCK]
+        la[at] = 0
 
 
 def test_host_side_argument_errors():
@@ -112,10 +121,10 @@ def test_bench_inputs(N):
     check(typ, la, size, 4096, 0, need)
 
 
-@pytest.mark.parametrize("N", [1000, 69938, 300000])
+@pytest.mark.parametrize("N", [1000, 69938, 300000, *RADIX])
 def test_no_writes_past_outputs_or_workspace(N):
-    """Sentinels past order[N], prefix[N], result[2] and the workspace's stated
-    size are untouched (both radix pass forms)."""
+    """Sentinels past order[N], prefix[N], result[2], the workspace's stated size
+    and the part of it that the form of this size lays out are untouched."""
     rng = np.random.default_rng(N + 5)
     typ, la, size = eviction_blocks(rng, N, programs=300, tie_frac=0.4, var_size=True)
     dev = "cuda"
@@ -134,7 +143,8 @@ def test_no_writes_past_outputs_or_workspace(N):
                               result.data_ptr(), torch.cuda.current_stream().cuda_stream) == M.MORI_OK
     torch.cuda.synchronize()
     assert (order[N:] == -7).all().item() and (prefix[N:] == -9).all().item() and (result[2:] == -11).all().item()
-    assert (ws[wbytes:] == 0x3C).all().item()
+    used = 0 if N <= lib().direct_max() else lib().bucket_bytes(N) if N <= lib().bucket_max() else lib().radix_bytes(N)
+    assert used <= wbytes and (ws[used:] == 0x3C).all().item()
     assert result[1].item() == 0
 
 
@@ -157,20 +167,37 @@ def test_python_wrapper():
     assert result.cpu().tolist() == [o_count, 0]
 
 
-def test_need_at_prefix_edges():
+@pytest.mark.parametrize("N", [5000, 70000, *RADIX])
+def test_need_at_prefix_edges(N):
     """The eviction count when need is 0, equals a prefix value exactly (at the
-    first block, at tile edges, at the last block), lies just above one, or
-    exceeds every block's bytes: each equals the oracle's."""
+    first block, at edges of tiles or of buckets, at the last block), lies just
+    above one, or exceeds every block's bytes: each equals the oracle's."""
     rng = np.random.default_rng(5)
-    N = 5000  # five tiles of 1024 keys
     typ, la, size = eviction_blocks(rng, N, programs=40, tie_frac=0.5, var_size=True)
-    rc, _, prefix, _ = oracle.evict_order(typ, la, 0, 0, size=size, unit_bytes=1)
+    rc, order, prefix, _ = oracle.evict_order(typ, la, 0, 0, size=size, unit_bytes=1)
     assert rc == oracle.OK
     p = [int(x) for x in prefix]
-    for need in (0, 1, p[0], p[0] + 1, p[1022], p[1023], p[1023] + 1, p[1024], p[2047], p[4095], p[-2], p[-1],
-                 p[-1] + 1, 10 * p[-1]):
-        log(f"evict need={need}")
-        check(typ, la, size, 1, 0, need)
+    place = np.empty(N, np.int64)
+    place[order] = np.arange(N)
+    if N <= lib().direct_max():
+        edges = [1023, 1024, 2048, 4096]
+    elif N <= lib().bucket_max():
+        starts = bucket_starts(N, lambda ids: place[ids])
+        edges = [int(e) for e in (starts[1], starts[2], starts[len(starts) // 2], starts[-2])]
+    else:
+        edges = [2048, 4096, N // 4096 * 2048, N // 2048 * 2048]
+    needs = [0, 1, p[0], p[0] + 1, p[-2], p[-1], p[-1] + 1, 10 * p[-1]]
+    for e in edges:
+        needs += [p[e - 2] + 1, p[e - 1], p[e - 1] + 1, p[e], p[e] + 1]
+    for need in needs:
+        log(f"evict N={N} need={need}")
+        count = 0 if need == 0 else min(int(np.searchsorted(prefix, np.uint64(need))) + 1, N)
+        g_order, g_prefix, res = run_gpu(typ, la, size, 1, 0, need)
+        assert np.array_equal(g_order, order) and np.array_equal(g_prefix, prefix)
+        assert list(res) == [count, 0], (need, res, count)
+    for need in (0, p[edges[0] - 1], p[-1] + 1):  # the counts above against the oracle's own
+        count = 0 if need == 0 else min(int(np.searchsorted(prefix, np.uint64(need))) + 1, N)
+        assert oracle.evict_order(typ, la, 0, need, size=size, unit_bytes=1)[3] == count
 
 
 def test_more_tiles_than_the_single_kernel_tail():

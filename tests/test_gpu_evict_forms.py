@@ -118,7 +118,7 @@ def test_packing_limit(span):
     check(np.zeros(N, np.uint8), la, None, 16, 0, 16 * (N - 1) + 1)
 
 
-@pytest.mark.parametrize("N", [3000, 50000])
+@pytest.mark.parametrize("N", [3000, 50000, (1 << 20) + 5000, (1 << 21) + 5000])
 def test_invalid_block_and_no_prefix(N):
     rng = np.random.default_rng(N)
     typ, la, size = eviction_blocks(rng, N, programs=40, tie_frac=0.5, var_size=True)

@@ -17,7 +17,7 @@ from workload import eviction_blocks
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N", [69938, 1 << 20])  # one look-back kernel per pass / three kernels per pass
+@pytest.mark.parametrize("N", [4096, 69938, 1 << 20, (1 << 20) + 5000])  # direct, buckets twice, radix passes
 def test_eviction_order_replayed_from_a_graph(N):
     rng = np.random.default_rng(N + 11)
     draws = [eviction_blocks(rng, N, programs=1024, tie_frac=0.5, var_size=True) for _ in range(4)]
