@@ -630,7 +630,7 @@ int translate(mori_ctx* c, int d, const uint64_t* addr, hipStream_t s) {
 uint32_t grid_direct(const mori_ctx* c, bool device_only) {
   if (!device_only) return kGridHost;
   const uint64_t units = std::min<uint64_t>(c->tbl_len, c->pool.num_blocks) * c->LC;
-  const uint64_t need = units / swap_runs_per_workgroup(c->run, false) + 1;
+  const uint64_t need = units / swap_runs_per_workgroup(c->run) + 1;
   return (uint32_t)std::min<uint64_t>(need, c->run >= (32u << 10) ? 32768u : 16384u);
 }
 

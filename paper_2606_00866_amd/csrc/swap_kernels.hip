@@ -207,24 +207,31 @@ struct CopyShape {
 // Between HBM buffers, runs of 2048 vectors (32 KiB) and more: one per
 // workgroup, LONG_VEC vectors per thread per round (a 72 KiB run takes a
 // round of 64 KiB and one of 8 KiB; a 32 KiB run one round, half of it
-// clamped).  Shorter runs: one round each, as many per workgroup (a power of
-// two, at most one per wavefront) as give each thread two vectors when that
-// comes out even (power-of-two runs), else four; a run within one wavefront's
-// 64 lanes one.  One vector per thread keeps too little in flight there: a
-// pair of rebalances of 1.5 GiB takes 1.43 ms with one, 1.25 with two on
-// 4 KiB runs, 1.87 with one, 1.26 with four on 10.25 KiB runs, 1.55 and 1.24
-// on 18 KiB runs.  Over the host link (kernel-direct mode), runs of 1024
-// vectors and more: two per workgroup, one vector per thread per round;
-// shorter ones one vector per thread.  Measured in the full-size pipelined
-// rebalance: between HBM buffers four vectors per thread beat one to three,
-// five and eight on runs of 32 and 72 KiB; over the host link four or two
-// vectors per thread lose 12% or 7% against one (fewer accesses in flight suit
-// the link's two directions), and two runs per workgroup gain 1%.
-CopyShape copy_shape(uint64_t run, bool host_link) {
+// clamped).  Shorter runs, as many per workgroup as fit it (a power of two, at
+// most one per wavefront):
+//   kernel-direct: one round each with two vectors per thread when that comes
+//     out even (power-of-two runs), else four; a run within one wavefront's 64
+//     lanes one.  One vector per thread keeps too little in flight there: a
+//     pair of rebalances of 1.5 GiB takes 1.43 ms with one, 1.25 with two on
+//     4 KiB runs, 1.87 with one, 1.26 with four on 10.25 KiB runs, 1.55 and
+//     1.24 on 18 KiB runs;
+//   to and from staging: one vector per thread.  Beside the copy engines and at
+//     times the other direction's kernel, less in flight is faster (pipelined
+//     rebalance, TB/s of gather and scatter with two vectors -> one: 16 KiB
+//     runs 5.4 and 5.15 -> 5.7 and 5.5, 4 KiB runs 5.45 and 5.15 -> 5.7 and 5.45).
+// Over the host link (kernel-direct mode), runs of 1024 vectors and more: two
+// per workgroup, one vector per thread per round; shorter ones one vector per
+// thread.  Measured in the full-size pipelined rebalance: between HBM buffers
+// four vectors per thread beat one to three, five and eight on runs of 32 and
+// 72 KiB; over the host link four or two vectors per thread lose 12% or 7%
+// against one (fewer accesses in flight suit the link's two directions), and
+// two runs per workgroup gain 1%.
+enum class Side { kHbm, kStaging, kHost };
+CopyShape copy_shape(uint64_t run, Side side) {
   const uint64_t n16 = run / 16;
-  if (host_link && n16 >= NT) return {2, 1};
-  if (!host_link && n16 >= 2 * NT) return {1, LONG_VEC};
-  const uint32_t vec = host_link || n16 <= 64 ? 1 : n16 <= 128 || (n16 & (n16 - 1)) == 0 ? 2 : 4;
+  if (side == Side::kHost && n16 >= NT) return {2, 1};
+  if (side != Side::kHost && n16 >= 2 * NT) return {1, LONG_VEC};
+  const uint32_t vec = side != Side::kHbm || n16 <= 64 ? 1 : n16 <= 128 || (n16 & (n16 - 1)) == 0 ? 2 : 4;
   uint32_t per = 1;
   while (per < MAX_RUNS_PER_PASS && 2ull * per * n16 <= (uint64_t)NT * vec) per *= 2;
   return {per, vec};
@@ -246,7 +253,7 @@ void launch_per(uint32_t vec, const SwapArgs& a, uint32_t grid, hipStream_t s) {
 
 template <bool kOut>
 hipError_t launch_swap(const SwapArgs& a, uint32_t grid, hipStream_t s) {
-  const CopyShape sh = copy_shape(a.run, a.host_link != 0);
+  const CopyShape sh = copy_shape(a.run, a.host_link ? Side::kHost : a.staging ? Side::kStaging : Side::kHbm);
   switch (sh.per) {
     case 1:
       if (sh.vec == 1) launch_shape<kOut, 1, 1>(a, grid, s);
@@ -262,7 +269,7 @@ hipError_t launch_swap(const SwapArgs& a, uint32_t grid, hipStream_t s) {
 
 }  // namespace
 
-uint32_t swap_runs_per_workgroup(uint64_t run, bool host_link) { return copy_shape(run, host_link).per; }
+uint32_t swap_runs_per_workgroup(uint64_t run) { return copy_shape(run, Side::kHbm).per; }
 
 hipError_t launch_swap_out(const SwapArgs& a, uint32_t grid, hipStream_t s) { return launch_swap<true>(a, grid, s); }
 

@@ -1,8 +1,9 @@
-"""Kernel-direct swaps at the edges of the copy shapes and of the unit decode:
+"""Swaps at the edges of the copy shapes and of the unit decode:
 runs on both sides of every shape's limit, and hundreds of programs of zero to
 three blocks, so that a grid stride passes many programs and both parts of a
-swap-in begin and end inside the list.  Buffers in registered device memory and
-in pinned host memory; every resident byte against the oracle."""
+swap-in begin and end inside the list.  Kernel-direct with buffers in registered
+device memory and in pinned host memory, and through staging; every resident
+byte against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -19,9 +20,10 @@ pytestmark = pytest.mark.gpu
 VECTORS = [1, 64, 65, 128, 129, 256, 257, 656, 1023, 1024, 1025, 2047, 2048, 4608]
 
 
-@pytest.mark.parametrize("where", ["device", "host"])
+@pytest.mark.parametrize("where", ["device", "host", "staging"])
 @pytest.mark.parametrize("vectors", VECTORS)
 def test_many_small_programs(vectors, where):
+    mode = M.MORI_COPY_CE if where == "staging" else M.MORI_COPY_KERNEL
     rng = np.random.default_rng(vectors)
     geom = Geometry(layers=3, planes=1, block_tokens=1, row_bytes=16 * vectors, num_blocks=0)
     inst = random_instance(rng, P=300 if vectors < 1000 else 80, max_blocks=3, geom=geom, tier_p=(0.55, 0.45),
@@ -54,8 +56,8 @@ def test_many_small_programs(vectors, where):
             assert res.rc == oracle.OK
             assert tp.rank_partition(gpu_bytes=bg, cpu_bytes=inst.total_bytes, window=torch.from_numpy(w).cuda(),
                                      stream=s_out) == 0
-            assert M.mori_kv_swap_out(tp.ctx, addr.ctypes.data, M.MORI_COPY_KERNEL, s_out.cuda_stream) == M.MORI_OK
-            assert M.mori_kv_swap_in(tp.ctx, addr.ctypes.data, M.MORI_COPY_KERNEL, s_in.cuda_stream) == M.MORI_OK
+            assert M.mori_kv_swap_out(tp.ctx, addr.ctypes.data, mode, s_out.cuda_stream) == M.MORI_OK
+            assert M.mori_kv_swap_in(tp.ctx, addr.ctypes.data, mode, s_in.cuda_stream) == M.MORI_OK
             torch.cuda.synchronize()
             assert M.mori_query(tp.ctx, M.MORI_Q_DEVICE_ERROR) == (M.MORI_OK, 0)
             rc, plan = tp.plan_wait()
