@@ -771,11 +771,14 @@ __global__ __launch_bounds__(RT) void rank_partition_kernel(PlanArgs a) {
 
 hipError_t launch_rank(const PlanArgs& a, hipStream_t s) {
   static_assert(1024 * 4 == (int)MORI_MAX_PROGRAMS, "the large shape holds every program");
-  // workgroup 0 ranks; the others (about two table entries per thread) find the
-  // pages' owners
+  // workgroup 0 ranks; the others (about two table entries per thread, at most
+  // 2^21 threads in all) find the pages' owners.  With at most 2048 workgroups
+  // whatever their size, the one-wave shape kept too few accesses in flight: a
+  // pair of plans of 64 programs over 1 M, 2 M, 4 M pages 119, 177, 275 us, with
+  // the bound on threads 109, 147, 211; of 256 over 4 M 238 -> 215.
   auto grid = [&](uint32_t rt) {
-    const uint64_t g = ((uint64_t)a.tbl_len + 2ull * rt - 1) / (2ull * rt);
-    return dim3(1 + (uint32_t)(g < 2048 ? g : 2048));
+    const uint64_t g = ((uint64_t)a.tbl_len + 2ull * rt - 1) / (2ull * rt), most = (1u << 21) / rt;
+    return dim3(1 + (uint32_t)(g < most ? g : most));
   };
   const bool counted = a.P > SORT_MAX_PROGRAMS || (uint64_t)a.P * a.k > SORT_MAX_CYCLES;
   if (counted) {
