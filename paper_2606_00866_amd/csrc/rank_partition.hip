@@ -22,9 +22,9 @@
 //      swap-out and swap-in lists in that order and the page/slot bases.
 //
 // P <= 4096 programs fit in LDS (4 per thread), so placement and diff are one
-// launch, for up to 1024 programs the whole step (5 us for tens of programs, 7
-// for 256), bound by the one workgroup's vector ALU and barriers; nothing here
-// is bandwidth-bound.
+// launch, for up to 1024 programs with windows of up to 2^14 cycles in all the
+// whole step (5 us for tens of programs, 7 for 256), bound by the one workgroup's
+// vector ALU and barriers; nothing here is bandwidth-bound.
 #include "mori_internal.h"
 #include "sort.h"
 #include "wave.h"
@@ -39,8 +39,9 @@ namespace {
 // SORT_MAX_PROGRAMS programs itself; above, and where the windows together hold
 // more than SORT_MAX_CYCLES cycles, two kernels before it do that on many
 // compute units.  Those cost about 4.5 us a plan; the one workgroup took 13 us
-// to sort 4096 programs (radix passes; merging is bound by LDS gathers and no
-// faster there) and takes 0.5 ns for each cycle it reads.  A pair of plans,
+// to sort 4096 programs in radix passes (merging them was not built: 54 LDS
+// gathers for each of 64 waves, at about 10 clocks, come to 14 us) and takes
+// 0.5 ns for each cycle it reads.  A pair of plans,
 // sorted -> counted: 4096 programs with 5 cycles each 112 -> 100 us, with 64
 // 380 -> 108; 1100 programs 92 -> 81 and 150 -> 86; 1024 programs with 5 stay
 // at 72, with 64 go from 134 to 85, 300 with 64 stay at 82.

@@ -53,9 +53,7 @@ __device__ inline void sort_wave(uint64_t& key, uint32_t& id, uint32_t n = 64) {
 // Place of entry (key, id), now at x of s_key[0, m) (and s_id unless PACKED),
 // when each list of L entries is merged with its sibling: its place in its own
 // list plus, by binary search, the sibling's entries below it.  The sibling may
-// end early or lie past m altogether; both its ends are clamped, because the
-// compiler dropped the test of `sib < m ? min(L, m - sib) : 0` (it took the
-// subtraction not to wrap) and the search read past the entries.
+// end early or lie past m altogether, so both its ends are clamped.
 template <bool PACKED>
 __device__ inline uint32_t merged_place(const uint64_t* s_key, const uint32_t* s_id, uint32_t m, uint32_t L, uint32_t x,
                                         uint64_t key, uint32_t id) {

@@ -70,7 +70,7 @@ def test_workspace_holds_every_form():
     bucket form's need never falls with more blocks (a fixed array sized for the
     most blocks holds any fewer)."""
     L = lib()
-    sizes = [L.direct_max() + 1, 8500, 16384, 32768, 32769, 69938, 1 << 18, (1 << 18) + 1, 1 << 19, (1 << 20) - 1, 1 << 20]
+    sizes = [L.direct_max() + 1, 8500, 16384, 32768, 32769, 69938, 1 << 18, (1 << 18) + 1, 1 << 19, L.bucket_max()]
     need = [L.bucket_bytes(N) for N in sizes]
     assert need == sorted(need)
     assert all(L.workspace_bytes(N) >= n for N, n in zip(sizes, need))

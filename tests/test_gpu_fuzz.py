@@ -4,10 +4,10 @@ key, three tiers, the incremental policy), random geometries and pool
 fragmentation, random budgets, both copy modes and small staging buffers
 (many chunks), several steps per pool, all through the C ABI and compared
 element by element (plan, tables, tiers, free map, every resident and host
-byte).  Then eviction orders at sizes on both sides of the switch between the
-one-kernel and the three-kernel radix passes, pools whose policy changes from
-step to step, and pools of 700-4096 programs (the rank kernel's radix-sort
-shapes) with windows of 1 to 64 cycles."""
+byte).  Then eviction orders at sizes on both sides of the switches between its
+forms, pools whose policy changes from step to step, and pools of 700-4096
+programs (sorted by one workgroup or ranked by many) with windows of 1 to 64
+cycles."""
 import numpy as np
 import pytest
 import torch
@@ -84,7 +84,7 @@ def test_random_rebalances(block):
             pair.close()
 
 
-@pytest.mark.parametrize("N", [1, 1023, 1024, 1025, 131071, 131072, 131073, 200000])
+@pytest.mark.parametrize("N", [1, 1023, 1024, 1025, 8192, 8193, 131071, 131072, 131073, 200000, 1 << 20, (1 << 20) + 1])
 def test_eviction_sizes_around_the_pass_switch(N):
     from test_gpu_evict import check
 

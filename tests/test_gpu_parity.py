@@ -329,7 +329,7 @@ def test_buffers_in_other_registered_ranges(where, mode, row_bytes, tokens):
     """CPU-tier buffers in a registered device-memory range (AUTO then resolves
     to the kernels at the device grid and its copy shapes: 256 B runs sixteen
     to a workgroup, 72 KiB runs in rounds of four vectors per thread, 16 KiB
-    runs one vector per thread) or alternating between two pinned host ranges
+    runs two to a workgroup and two vectors per thread) or alternating between two pinned host ranges
     registered beside the pool's arena: tables, tiers, free map, resident pages
     and every buffer byte equal the oracle's over three steps; then the range
     limit (ENOSPC) and unknown memory (EINVAL)."""
@@ -576,14 +576,14 @@ def test_pools_around_the_tile_scan_switch(target):
                                                (16, 4)],
                          ids=["32KiB", "24KiB", "16KiB", "8KiB", "4KiB", "2KiB", "64B"])
 def test_runs_per_pass(row_bytes, tokens, mode):
-    """Runs of 32 KiB (between HBM buffers one round of four vectors per
-    thread, half of them past the run's end), 24 KiB and 16 KiB (one vector
-    per thread per round: two rounds, the second half past the end, and one;
-    over the host link two runs per workgroup), and runs a workgroup copies
-    several at a time, one vector per thread: 8, 4 and 2 KiB (two, four and
-    eight per pass) and 64 B (sixteen, most threads past the end): every byte
-    lands where the oracle puts it, three steps with swaps both ways, in both
-    copy modes."""
+    """Through staging, runs of 32 KiB (one round of four vectors per thread,
+    half of them past the run's end), 24 KiB and 16 KiB (one vector per thread
+    per round: two rounds, the second half past the end, and one), and runs a
+    workgroup copies several at a time, one vector per thread: 8, 4 and 2 KiB
+    (two, four and eight per pass) and 64 B (sixteen, most threads past the
+    end); over the host link the same, but two runs per workgroup from 16 KiB
+    on: every byte lands where the oracle puts it, three steps with swaps both
+    ways, in both copy modes."""
     rng = np.random.default_rng(row_bytes * 100 + tokens)
     geom = Geometry(layers=2, planes=2, block_tokens=tokens, row_bytes=row_bytes, num_blocks=0)
     inst = random_instance(rng, P=40, max_blocks=12, geom=geom, tier_p=(0.5, 0.3, 0.2), extra_free=20)
@@ -684,8 +684,9 @@ def test_plans_supersede_without_swaps():
 @pytest.mark.parametrize("P", [63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 4095, 4096])
 def test_program_counts_at_the_shape_switches(P):
     """Program counts on both sides of each switch between the rank kernel's
-    shapes (one wave up to 64 and 256 threads up to 256, both counting ranks
-    directly; one item per thread up to 1024, four above): boundary,
+    shapes (one wave up to 64, 256 threads up to 256, 1024 above; one item per
+    thread and sorted there up to 1024, four and ranked by other workgroups
+    above): boundary,
     incremental and skip-fit plans with exact ties, equal to the oracle."""
     rng = np.random.default_rng(P)
     geom = Geometry(layers=1, planes=2, block_tokens=1, row_bytes=16, num_blocks=0)
