@@ -358,9 +358,9 @@ int mori_evict_workspace(uint32_t num_blocks, uint64_t* bytes);
  * less, 0 when need_bytes is 0), MORI_DEV_* error bits}.  The time depends
  * little on how types and times lie over the block ids; only times made to miss
  * the blocks the call samples make it long (2^20 blocks: up to 9 ms).
- * workspace: device
- * memory of at least mori_evict_workspace bytes, 256-B aligned, owned by the
- * caller and used only while the call's work runs.  Nothing is allocated.
+ * workspace: device memory of at least mori_evict_workspace bytes, 256-B
+ * aligned, owned by the caller and used only while the call's work runs.
+ * Nothing is allocated.
  * EINVAL: null pointers, misaligned or short workspace, bad tier. */
 int mori_evict_order(const mori_blocks* blocks, uint32_t tier, uint64_t need_bytes, void* workspace,
                      uint64_t workspace_bytes, uint32_t* order, uint64_t* prefix, uint32_t* result,
